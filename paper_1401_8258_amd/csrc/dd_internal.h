@@ -1,6 +1,7 @@
 // Internal declarations shared by the host plan code and the HIP launch code.
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 #include <string>
 #include <vector>
@@ -62,6 +63,39 @@ Launch choose_launch_prod(int32_t max_span, int nchan, int cs_req, int64_t lds_c
 
 inline int64_t align_up(int64_t x, int64_t a = kAlign) { return (x + a - 1) / a * a; }
 
+// Shared-sum form (csrc/shared.hip): words of a time tile (4 rows x 63 lanes x 4).
+constexpr int kShWords = 1008;
+// Trials per wavefront, and wavefronts that a CU holds: FP32 and FP16 sums fit 128 registers
+// (16 wavefronts); 8-bit input keeps two totals per word and takes 168 (12 wavefronts).
+constexpr int kShG = 2;
+constexpr int sh_max_waves(int dtype) { return dtype == DD_U8 ? 12 : 16; }
+// 16-byte window chunks a wavefront forms per row: lanes past it lack a neighbour's words.
+constexpr int sh_row_chunks(int dtype) { return dtype == DD_U8 ? 62 : 63; }
+constexpr int kShMaxPat = 15;     // patterns of a bundle
+constexpr int kShMaxE = 3;        // largest shift of a channel in a pattern
+constexpr int kShMaxBundles = 4;  // bundles of a stage
+constexpr int kShBlock = 132;     // bytes of code per pattern block
+constexpr int kShSpare = 1024;    // LDS bytes before the stages: where lanes without a chunk write
+// A stage's record. Lane l's four ints, for forming: x the code offset of pattern l % 16 of
+// bundle l / 16 (pattern * kShBlock; past the last one 64 * kShBlock); y, z the window start
+// and the channel of (bundle, channel) l (lanes 0-15); w per bundle {channels | patterns << 8,
+// bytes per pattern, LDS offset, 0} at 4 b, all bundles' rows and the four bundles' rows in
+// bytes at kShLaneRows, and the samples past a window's start that a row may load at
+// kShLaneReach. Then per wavefront kShAddInts ints, for adding: its trials' LDS offsets (byte
+// offset of the window's 16-byte boundary | words past it) in bundle order, and in the last
+// int bundles << 1 | fold.
+constexpr int kShFormInts = 256;
+constexpr int kShAddInts = 16;
+constexpr int kShLaneRows = 16;
+constexpr int kShLaneReach = 18;
+constexpr int sh_stage_ints(int nw) { return kShFormInts + kShAddInts * nw; }
+struct Shared {
+  bool on = false;
+  int32_t nw = 0;      // wavefronts per workgroup
+  int32_t mirror = 0;  // samples past a window's start that a unit may read
+  int64_t lds = 0;     // bytes (the spare slot and two stages)
+};
+
 struct Tiles {
   int32_t g;   // DM trials per wavefront
   int32_t w;   // wavefronts per workgroup (each on its own G trials)
@@ -88,6 +122,10 @@ struct dd_plan {
   int32_t max_span = 0;             // max over channels and groups of the in-group delay spread
   dd::Launch launch{};               // kernel geometry (fixed at plan time: the offsets depend on it)
   uint64_t id = 0;
+  // Plans without a tuning run in the shared-sum form where it pays (sh.on); tiles and launch
+  // then describe the form the plan would otherwise take, and dms_per_group, ngroups and
+  // dev_table belong to the shared-sum form.
+  dd::Shared sh;
 };
 
 struct dd_stream {
@@ -134,10 +172,16 @@ WsLayout workspace_layout(const dd_plan* p, int64_t n, bool linear = true);
 int64_t ring_table_bytes(const dd_plan* p);
 // Samples after a ring row's R that mirror its start, so no channel window the kernel
 // reads (at most launch.L + 3 samples from any start in [0, R)) wraps.
-inline int64_t ring_mirror(const dd_plan* p) { return (int64_t)p->launch.L + 64; }
+inline int64_t ring_mirror(const dd_plan* p) {
+  return std::max<int64_t>((int64_t)p->launch.L + 64, p->sh.on ? p->sh.mirror : 0);
+}
 inline int64_t ring_len_for(const dd_plan* p, int64_t block) { return align_up(block + (int64_t)p->maxdelay, 64); }
 // Rows a stream's ring keeps per channel: the direct-read form keeps its four shifted copies.
-inline int64_t ring_copies(const dd_plan* p) { return p->launch.form == kFormDirect ? 4 : 1; }
+inline bool runs_direct(const dd_plan* p) { return p->launch.form == kFormDirect && !p->sh.on; }
+inline int64_t ring_copies(const dd_plan* p) { return runs_direct(p) ? 4 : 1; }
+// Statistics partials per series: one per time tile of the kernel that runs.
+inline int64_t stat_tile(const dd_plan* p) { return !p->sh.on ? kTile : p->dtype == DD_U8 ? 2 * kShWords : kShWords; }
+inline int64_t stat_tiles(const dd_plan* p, int64_t nout) { return (nout + stat_tile(p) - 1) / stat_tile(p); }
 int64_t elem_bytes(int32_t dtype);
 // kFormRegWin device table: [ngroups][nchan] group first delays, then from this int32
 // offset [ngroups][nchan][8 wavefronts] int4 {window byte offset, trial indices 0-3, 4-7, 0},
@@ -158,6 +202,11 @@ struct InView {
 // Launch of the register-window kernel for nout outputs (statistics partials into part
 // when non-null); defined with the kernel.
 int launch_regwin(const dd_plan* p, const InView& in, const int32_t* d_table, int64_t nout, float* out,
+                  int64_t out_stride, double* part, void* stream);
+// Shared-sum form: fills sh, the groups and the device table and returns true, or leaves the
+// plan as it is and returns false where that form would not pay.
+bool plan_shared(dd_plan* p, int64_t lds_cap);
+int launch_shared(const dd_plan* p, const InView& in, const int32_t* d_table, int64_t nout, float* out,
                   int64_t out_stride, double* part, void* stream);
 // Direct-read form (8-bit input): device table [nchan][ndm_pad] of plain delays (padded trials
 // repeat the last DM). Fills the plan's tiles, groups, launch and table.

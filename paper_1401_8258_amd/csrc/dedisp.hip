@@ -1174,7 +1174,7 @@ int copy_tail(const KParams& P, hipStream_t st) {
 // Statistics finalize and candidate kernels for one plan's nout outputs.
 int launch_tail(const dd_plan* p, int64_t nout, const Outputs& o, char* ws, const dd::WsLayout& l, hipStream_t st) {
   if (!(o.mean && o.rms)) return DD_OK;
-  const int64_t ntiles = (nout + kTile - 1) / kTile;
+  const int64_t ntiles = dd::stat_tiles(p, nout);
   double* part = reinterpret_cast<double*>(ws + l.part_off);
   double* stat = reinterpret_cast<double*>(ws + l.thr_off);
   hipLaunchKernelGGL(stats_finalize, dim3((unsigned)((p->ndm + 3) / 4)), dim3(256), 0, st, part, ntiles,
@@ -1206,9 +1206,10 @@ int set_lds(const void* k, int64_t lds) {
 // Dedisperse nout outputs of a prepared input view, then stats and candidates.
 int run_pipeline(const dd_plan* p, const InView& in, const int32_t* d_table, int64_t nout, const Outputs& o,
                  char* ws, const dd::WsLayout& l, hipStream_t st, bool tail) {
-  if (p->launch.form == dd::kFormRegWin || p->launch.form == dd::kFormDirect) {
+  if (p->sh.on || p->launch.form == dd::kFormRegWin || p->launch.form == dd::kFormDirect) {
     double* part = (o.mean && o.rms) ? reinterpret_cast<double*>(ws + l.part_off) : nullptr;
-    int rc = p->launch.form == dd::kFormRegWin
+    int rc = p->sh.on ? dd::launch_shared(p, in, d_table, nout, o.out, o.out_stride, part, st)
+             : p->launch.form == dd::kFormRegWin
                  ? dd::launch_regwin(p, in, d_table, nout, o.out, o.out_stride, part, st)
                  : dd::launch_direct(p, in, d_table, nout, o.out, o.out_stride, part, ws + l.quad_off, st);
     if (rc) return rc;
@@ -1376,8 +1377,11 @@ int dd_dedisperse_noalloc(const dd_plan* p, const void* d_in, int64_t nsamp, int
   // the workspace regions after the delay table, moved to the start of the scratch array
   dd::WsLayout l = dd::workspace_layout(p, nsamp);
   const int64_t base = l.part_off;
-  if (l.total - base > kScratchBytes)
-    return dd::fail(DD_ERR_UNSUPPORTED, "this call needs " + std::to_string(l.total - base) +
+  // 8-bit plans in the shared-sum form keep the limit of their four-copies form
+  const int64_t copies =
+      p->sh.on && p->launch.form == dd::kFormDirect ? 4 * (int64_t)p->nchan * dd::direct_quad_row(nsamp) : 0;
+  if (l.total - base + copies > kScratchBytes)
+    return dd::fail(DD_ERR_UNSUPPORTED, "this call needs " + std::to_string(l.total - base + copies) +
                                             " bytes of scratch; the static scratch holds " +
                                             std::to_string(kScratchBytes));
   l.part_off -= base;
@@ -1457,7 +1461,7 @@ int dd_stream_append(dd_stream* s, const void* d_block, int64_t nsamp, int64_t i
   char* ring = static_cast<char*>(s->ring) + dd::ring_table_bytes(p);
   const int64_t mirror = s->ring_row - s->ring_len;
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const bool quad = p->launch.form == dd::kFormDirect;
+  const bool quad = dd::runs_direct(p);
   if (seq > s->next_seq) {
     // lost blocks: block samples of zeros each; only the last ring length of them can still
     // be read, so only those are written
@@ -1607,6 +1611,9 @@ int dd_batch_dedisperse(const dd_batch_item* items, int32_t n, void* d_workspace
   std::vector<Outputs> outs((size_t)n);
   std::vector<int64_t> nouts((size_t)n);
   std::vector<dd::WsLayout> lays((size_t)n);
+  std::vector<int32_t> shared;  // shared-sum items
+  std::vector<InView> views((size_t)n);
+  std::vector<const int32_t*> tables((size_t)n);
   for (int32_t i = 0; i < n; ++i) {
     const dd_batch_item& it = items[i];
     dd_stream* sp = it.stream_item;
@@ -1616,7 +1623,7 @@ int dd_batch_dedisperse(const dd_batch_item* items, int32_t n, void* d_workspace
     if (p->launch.form == dd::kFormRegWin)
       return dd::fail(DD_ERR_UNSUPPORTED, "batch item " + std::to_string(i) +
                                               ": register-window plans are not batched; use DD_FORM_LDS");
-    const bool is_direct = p->launch.form == dd::kFormDirect;
+    const bool is_direct = dd::runs_direct(p);
     InView in;
     const int32_t* table;
     int64_t nout, t_base = 0, lay_n;
@@ -1656,6 +1663,12 @@ int dd_batch_dedisperse(const dd_batch_item* items, int32_t n, void* d_workspace
     outs[i] = Outputs{it.d_out, it.out_row_stride, it.d_mean, it.d_rms, it.k_sigma, it.d_cand, it.cand_cap,
                       it.d_ncand, t_base};
     nouts[i] = nout;
+    if (p->sh.on) {
+      shared.push_back(i);
+      views[i] = in;
+      tables[i] = table;
+      continue;
+    }
     if (is_direct) {
       double* part = (it.d_mean && it.d_rms) ? reinterpret_cast<double*>(ws + lays[i].part_off) : nullptr;
       direct.push_back(dd::DirectItem{p, in, table, nout, it.d_out, it.out_row_stride, part, ws + lays[i].quad_off});
@@ -1763,6 +1776,14 @@ int dd_batch_dedisperse(const dd_batch_item* items, int32_t n, void* d_workspace
   const int64_t direct_desc = dd::direct_batch_desc_bytes(n);
   rc = dd::launch_direct_batch(direct, bw + lds_desc, direct_desc, st);
   if (rc) return rc;
+  for (int32_t i : shared) {
+    const dd_batch_item& it = items[i];
+    const dd_plan* p = it.stream_item ? it.stream_item->plan : it.plan;
+    char* ws = static_cast<char*>(it.d_plan_workspace);
+    double* part = (it.d_mean && it.d_rms) ? reinterpret_cast<double*>(ws + lays[i].part_off) : nullptr;
+    rc = dd::launch_shared(p, views[i], tables[i], nouts[i], it.d_out, it.out_row_stride, part, st);
+    if (rc) return rc;
+  }
   // statistics and candidates of every item: one launch per step for the whole batch
   std::vector<TailItem> tails, cands;
   int64_t nser = 0, nunit = 0;
@@ -1780,7 +1801,7 @@ int dd_batch_dedisperse(const dd_batch_item* items, int32_t n, void* d_workspace
     t.rms = o.rms;
     t.out = o.out;
     t.stride = o.out_stride;
-    t.ntiles = (nouts[i] + kTile - 1) / kTile;
+    t.ntiles = dd::stat_tiles(p, nouts[i]);
     t.nout = nouts[i];
     t.k = (double)o.k;
     t.ndm = p->ndm;

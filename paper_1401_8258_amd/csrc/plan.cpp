@@ -74,10 +74,10 @@ WsLayout workspace_layout(const dd_plan* p, int64_t nout, bool linear) {
   l.offs_off = o;
   o = align_up(o + (int64_t)p->ndm * l.nseg * 8 + 8);
   l.tail_off = o;
-  l.tail_bytes = p->dtype == DD_U8 && p->launch.form == kFormLds ? (int64_t)p->launch.L + 64 : 0;
+  l.tail_bytes = p->dtype == DD_U8 && p->launch.form == kFormLds && !p->sh.on ? (int64_t)p->launch.L + 64 : 0;
   o = align_up(o + 2 * l.tail_bytes);
   l.quad_off = o;
-  l.quad_bytes = linear && p->launch.form == kFormDirect ? 4 * (int64_t)p->nchan * direct_quad_row(nout) : 0;
+  l.quad_bytes = linear && runs_direct(p) ? 4 * (int64_t)p->nchan * direct_quad_row(nout) : 0;
   o = align_up(o + l.quad_bytes);
   l.total = o;
   return l;
@@ -306,6 +306,225 @@ int plan_direct(dd_plan* p, const Tiles& t) {
   return DD_OK;
 }
 
+// ------------------------------------------------------------------ shared-sum form
+
+namespace {
+
+// One bundle of 1..4 consecutive channels for one group of trials.
+struct Bundle {
+  int m = 0, np = 0, slot = 0, rows = 0;  // channels, patterns, bytes of a pattern's sums, rows
+  int32_t off[4] = {0, 0, 0, 0}, ch[4] = {0, 0, 0, 0};
+  uint8_t code[kShMaxPat] = {0};
+  std::vector<int32_t> trial;  // byte offset from the bundle's LDS base | words past 16 bytes
+  int64_t bytes() const { return (int64_t)np * slot; }
+  double cost = 0;
+};
+
+// Clocks of one CU: four 1 KB LDS reads per trial at 221 B/clk, and the sums' writes at 128
+// B/clk (both measured rates).
+constexpr double kShReadClk = 4 * 1024 / 221.0;
+
+// Channels c0 .. c0 + m - 1 for trials d0 .. d0 + n - 1 (past the last trial: the last one).
+// The reference channel is the bundle's smallest delay, so every relative delay is >= 0.
+// False when the patterns are too many or too wide, or the sums take more than cap bytes.
+bool make_bundle(const dd_plan* p, int c0, int m, int d0, int n, int64_t cap, Bundle* b) {
+  const int32_t ndm = p->ndm;
+  const int dl = std::min(d0 + n, (int)ndm) - 1;
+  const int32_t* row[4];
+  int ref = 0;
+  for (int j = 0; j < m; ++j) {
+    row[j] = &p->delays[(size_t)(c0 + j) * ndm];
+    if (row[j][dl] < row[ref][dl]) ref = j;
+  }
+  std::swap(row[0], row[ref]);
+  b->m = m;
+  for (int j = 0; j < m; ++j) b->ch[j] = c0 + j;
+  std::swap(b->ch[0], b->ch[ref]);
+  int32_t lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
+  for (int j = 1; j < m; ++j) {
+    lo[j] = hi[j] = row[j][d0] - row[0][d0];
+    for (int d = d0 + 1; d <= dl; ++d) {
+      const int32_t r = row[j][d] - row[0][d];
+      lo[j] = std::min(lo[j], r);
+      hi[j] = std::max(hi[j], r);
+    }
+    if (hi[j] - lo[j] > kShMaxE || lo[j] < 0) return false;
+  }
+  const int32_t k0 = row[0][d0];
+  const int64_t chunks = (int64_t)(row[0][dl] - k0) / 4 + 4 * 63 + 1;
+  b->slot = (int)std::min<int64_t>(16 * chunks, 1 << 24);
+  b->rows = (int)((chunks + sh_row_chunks(p->dtype) - 1) / sh_row_chunks(p->dtype));
+  if ((int64_t)b->slot > cap || b->rows > 63) return false;
+  for (int j = 0; j < m; ++j) b->off[j] = k0 + lo[j];
+  int8_t slot_of[256];
+  std::memset(slot_of, -1, sizeof(slot_of));
+  b->np = 0;
+  b->trial.resize((size_t)n);
+  for (int t = 0; t < n; ++t) {
+    const int d = std::min(d0 + t, dl);
+    uint32_t c = 0;
+    for (int j = 1; j < m; ++j) c |= (uint32_t)(row[j][d] - row[0][d] - lo[j]) << (2 * j);
+    if (slot_of[c] < 0) {
+      if (b->np == kShMaxPat) return false;
+      slot_of[c] = (int8_t)b->np;
+      b->code[b->np++] = (uint8_t)(c >> 2);  // the reference channel has no shift
+    }
+    const int32_t k = row[0][d] - k0;
+    b->trial[(size_t)t] = slot_of[c] * b->slot + (k & ~3) * 4 + (k & 3);
+  }
+  if (b->bytes() > cap) return false;
+  b->cost = n * kShReadClk + (double)b->bytes() / 128.0;
+  return true;
+}
+
+// Bundles of channels [c0, c1) (at most 4 channels): one of all, or its halves where that is
+// cheaper or the whole does not fit. False when even single channels do not fit.
+bool bundle_quad(const dd_plan* p, int c0, int c1, int d0, int n, int64_t cap, std::vector<Bundle>* out, double* cost) {
+  const int m = c1 - c0;
+  Bundle b;
+  const bool whole = m != 3 && make_bundle(p, c0, m, d0, n, cap, &b);
+  // a bundle of half the channels reads as much per trial: halves can only pay when the
+  // whole writes more than it saves
+  if (whole && (m == 1 || (double)b.bytes() / 128.0 <= n * kShReadClk)) {
+    out->push_back(std::move(b));
+    *cost += out->back().cost;
+    return true;
+  }
+  if (m == 1) return false;
+  std::vector<Bundle> h;
+  double hc = 0;
+  const int mid = c0 + (m == 4 ? 2 : m == 3 ? 2 : 1);
+  const bool halves = bundle_quad(p, c0, mid, d0, n, cap, &h, &hc) && bundle_quad(p, mid, c1, d0, n, cap, &h, &hc);
+  if (whole && (!halves || b.cost <= hc)) {
+    out->push_back(std::move(b));
+    *cost += out->back().cost;
+    return true;
+  }
+  if (!halves) return false;
+  for (Bundle& x : h) out->push_back(std::move(x));
+  *cost += hc;
+  return true;
+}
+
+}  // namespace
+
+// Device table: per group {offset, stages}, then the stages' records (dd_internal.h).
+bool plan_shared(dd_plan* p, int64_t lds_cap) {
+  const int32_t nchan = p->nchan, ndm = p->ndm;
+  const int fold = p->dtype == DD_U8 ? 256 : DD_CHAN_BLOCK;
+  const int maxw = sh_max_waves(p->dtype), G = kShG;
+  // Wavefronts per workgroup: one, two or four workgroups share a CU's wavefront slots and its
+  // LDS. More trials per workgroup share each sum, fewer keep windows short where delays
+  // grow by many samples per trial. The cheapest in LDS clocks per trial on a sample of the
+  // groups and channels wins.
+  int best_div = 0;
+  double best = 0;
+  for (int div = 1; div <= 4; div *= 2) {
+    const int n = G * (maxw / div);
+    if (div < 4 && ndm <= n / 2) continue;  // half the workgroup or more would be padding
+    const int64_t cap = (lds_cap / div - kShSpare) / 2 / 256 * 256;
+    const int ng = (ndm + n - 1) / n, nq = (nchan + 3) / 4;
+    const int gs = std::max(1, ng / 4), qs = std::max(1, nq / 16);
+    double cost = 0;
+    int64_t cnt = 0;
+    bool ok = true;
+    for (int g = ng - 1; g >= 0 && ok; g -= gs)
+      for (int q = nq - 1; q >= 0 && ok; q -= qs) {
+        std::vector<Bundle> v;
+        ok = bundle_quad(p, 4 * q, std::min(nchan, 4 * q + 4), g * n, n, cap, &v, &cost);
+        ++cnt;
+      }
+    if (!ok || !cnt) continue;
+    const double per = cost / ((double)cnt * n);
+    if (!best_div || per < best) best = per, best_div = div;
+  }
+  if (!best_div) return false;
+  const int nw = maxw / best_div, n = G * nw;
+  const int64_t cap = (lds_cap / best_div - kShSpare) / 2 / 256 * 256;
+  const int ng = (ndm + n - 1) / n;
+  const int ints = sh_stage_ints(nw);
+  std::vector<int32_t> tab((size_t)(2 * ng + 63) / 64 * 64, 0);
+  int64_t max_stage = 0, max_reach = 0;
+  std::vector<std::pair<size_t, int>> odd;  // records of odd stages and their bundles
+  for (int g = 0; g < ng; ++g) {
+    const size_t first = tab.size();
+    int nst = 0;
+    for (int f0 = 0; f0 < nchan; f0 += fold) {
+      const int f1 = std::min(nchan, f0 + fold);
+      std::vector<Bundle> v;
+      double cost = 0;
+      for (int q = f0; q < f1; q += 4)
+        if (!bundle_quad(p, q, std::min(f1, q + 4), g * n, n, cap, &v, &cost)) return false;
+      for (size_t i = 0; i < v.size();) {
+        // bundles that fit half the LDS share, within the block, as long as each wavefront has
+        // at most one row to form
+        size_t e = i + 1;
+        int64_t bytes = v[i].bytes();
+        int srows = v[i].rows;
+        while (e < v.size() && e - i < (size_t)kShMaxBundles && bytes + v[e].bytes() <= cap && srows + v[e].rows <= nw)
+          bytes += v[e].bytes(), srows += v[e++].rows;
+        const size_t at = tab.size();
+        tab.resize(at + (size_t)ints, 0);
+        int32_t* rec = &tab[at];
+        int64_t base = kShSpare, reach = 0;
+        int32_t rows = 0, packed = 0;
+        for (int l = 0; l < 64; ++l) rec[4 * l] = 64 * kShBlock;
+        for (size_t q = 0; q < e - i; ++q) {
+          const Bundle& b = v[i + q];
+          for (int j = 0; j < 4; ++j) {
+            // channels the bundle lacks repeat its first one (their samples are not used)
+            rec[4 * (4 * q + j) + 1] = b.off[j < b.m ? j : 0];
+            rec[4 * (4 * q + j) + 2] = b.ch[j < b.m ? j : 0];
+          }
+          for (int k = 0; k < b.np; ++k) rec[4 * (16 * q + k)] = b.code[k] * kShBlock;
+          int32_t* h = rec + 16 * q + 3;
+          h[0] = b.m | b.np << 8;
+          h[4] = b.slot;
+          h[8] = (int32_t)base;
+          rows += b.rows;
+          packed |= (int32_t)((uint32_t)b.rows << (8 * q));
+          reach = std::max<int64_t>(reach, 4 * ((int64_t)b.rows * sh_row_chunks(p->dtype) + 64) + 8 +
+                                               (p->dtype == DD_U8 ? kShWords : 0));
+          for (int w = 0; w < nw; ++w)
+            for (int t = 0; t < G; ++t)
+              rec[kShFormInts + kShAddInts * w + G * (int)q + t] = (int32_t)base + b.trial[(size_t)(G * w + t)];
+          base += b.bytes();
+        }
+        rec[4 * kShLaneRows + 3] = rows;
+        rec[4 * (kShLaneRows + 1) + 3] = packed;
+        rec[4 * kShLaneReach + 3] = (int32_t)reach;
+        for (int w = 0; w < nw; ++w)
+          rec[kShFormInts + kShAddInts * w + kShAddInts - 1] = (int32_t)(e - i) << 1 | (e == v.size() ? 1 : 0);
+        base -= kShSpare;
+        max_stage = std::max(max_stage, base);
+        max_reach = std::max(max_reach, reach);
+        if (nst & 1) odd.push_back({at, (int)(e - i)});
+        ++nst;
+        i = e;
+      }
+    }
+    tab[2 * (size_t)g] = (int32_t)first;
+    tab[2 * (size_t)g + 1] = nst;
+    if (tab.size() > ((size_t)1 << 29)) return false;
+  }
+  // odd stages use the second half of the LDS
+  for (const auto& o : odd) {
+    int32_t* rec = &tab[o.first];
+    for (int q = 0; q < o.second; ++q) rec[4 * (4 * q + 2) + 3] += (int32_t)max_stage;
+    for (int w = 0; w < nw; ++w)
+      for (int t = 0; t < G * o.second; ++t) rec[kShFormInts + kShAddInts * w + t] += (int32_t)max_stage;
+  }
+  p->sh.on = true;
+  p->sh.nw = nw;
+  p->sh.lds = kShSpare + 2 * max_stage;
+  p->sh.mirror = (int32_t)max_reach;
+  p->dms_per_group = n;
+  p->ngroups = ng;
+  p->ndm_pad = ng * n;
+  p->dev_table.swap(tab);
+  return true;
+}
+
 }  // namespace dd
 
 extern "C" {
@@ -366,6 +585,8 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
     t.cc = tuning->chan_stage;
     t.pw = tuning->producer_waves;
   }
+  // a plan without any choice of the caller's may run in the shared-sum form
+  const bool auto_form = form_req == DD_FORM_AUTO && !tiles_set;
   // 8-bit input takes the direct-read form unless the caller asks for another form or sets
   // an LDS-form tile field
   const bool direct = form_req == DD_FORM_DIRECT || (form_req == DD_FORM_AUTO && in_dtype == DD_U8 && !tiles_set);
@@ -417,6 +638,7 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
       delete p;
       return rc;
     }
+    if (auto_form) dd::plan_shared(p, lds_cap);
     p->id = g_next_id.fetch_add(1);
     *out = p;
     return DD_OK;
@@ -512,6 +734,7 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
       }
     }
   }
+  if (auto_form) dd::plan_shared(p, lds_cap);
   p->id = g_next_id.fetch_add(1);
   *out = p;
   return DD_OK;
