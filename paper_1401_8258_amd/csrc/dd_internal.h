@@ -73,21 +73,31 @@ constexpr int sh_max_waves(int dtype) { return dtype == DD_U8 ? 12 : 16; }
 constexpr int sh_row_chunks(int dtype) { return dtype == DD_U8 ? 62 : 63; }
 constexpr int kShMaxPat = 15;     // patterns of a bundle
 constexpr int kShMaxE = 3;        // largest shift of a channel in a pattern
+// Channels summed in one running FP32 sum before it joins the series' total. Sums of 4 to 128
+// channels, then of the 128-channel blocks, carry the rounding of about 23 adds at full size
+// for 1024 channels (32-channel blocks channel by channel: 32).
+constexpr int kShFold = 128;
+// FP32 plans of fewer channels keep the LDS form: their few, wide channels share little (8 to
+// 14 patterns per 16 to 32 trials at 64 channels, 4 at 1024), and their series stay those of
+// every explicit tiling, bit for bit.
+constexpr int kShMinChans = 128;
 constexpr int kShMaxBundles = 4;  // bundles of a stage
 constexpr int kShBlock = 132;     // bytes of code per pattern block
 constexpr int kShSpare = 1024;    // LDS bytes before the stages: where lanes without a chunk write
 // A stage's record. Lane l's four ints, for forming: x the code offset of pattern l % 16 of
 // bundle l / 16 (pattern * kShBlock; past the last one 64 * kShBlock); y, z the window start
 // and the channel of (bundle, channel) l (lanes 0-15); w per bundle {channels | patterns << 8,
-// bytes per pattern, LDS offset, 0} at 4 b, all bundles' rows and the four bundles' rows in
-// bytes at kShLaneRows, and the samples past a window's start that a row may load at
-// kShLaneReach. Then per wavefront kShAddInts ints, for adding: its trials' LDS offsets (byte
+// bytes per pattern, LDS offset, 0} at 4 b, the stage's rows at kShLaneRows, and the samples
+// past a window's start that a row may load at kShLaneReach; y from kShLaneMap on the stage's
+// rows, bundle | row of the bundle << 8. Then per wavefront kShAddInts ints, for adding: its trials' LDS offsets (byte
 // offset of the window's 16-byte boundary | words past it) in bundle order, and in the last
 // int bundles << 1 | fold.
 constexpr int kShFormInts = 256;
 constexpr int kShAddInts = 16;
 constexpr int kShLaneRows = 16;
-constexpr int kShLaneReach = 18;
+constexpr int kShLaneReach = 17;
+constexpr int kShLaneMap = 16;
+constexpr int kShMaxRows = 48;  // rows of a stage
 constexpr int sh_stage_ints(int nw) { return kShFormInts + kShAddInts * nw; }
 struct Shared {
   bool on = false;

@@ -354,7 +354,7 @@ bool make_bundle(const dd_plan* p, int c0, int m, int d0, int n, int64_t cap, Bu
   const int64_t chunks = (int64_t)(row[0][dl] - k0) / 4 + 4 * 63 + 1;
   b->slot = (int)std::min<int64_t>(16 * chunks, 1 << 24);
   b->rows = (int)((chunks + sh_row_chunks(p->dtype) - 1) / sh_row_chunks(p->dtype));
-  if ((int64_t)b->slot > cap || b->rows > 63) return false;
+  if ((int64_t)b->slot > cap || b->rows > kShMaxRows) return false;
   for (int j = 0; j < m; ++j) b->off[j] = k0 + lo[j];
   int8_t slot_of[256];
   std::memset(slot_of, -1, sizeof(slot_of));
@@ -411,7 +411,7 @@ bool bundle_quad(const dd_plan* p, int c0, int c1, int d0, int n, int64_t cap, s
 // Device table: per group {offset, stages}, then the stages' records (dd_internal.h).
 bool plan_shared(dd_plan* p, int64_t lds_cap) {
   const int32_t nchan = p->nchan, ndm = p->ndm;
-  const int fold = p->dtype == DD_U8 ? 256 : DD_CHAN_BLOCK;
+  const int fold = p->dtype == DD_U8 ? 256 : kShFold;
   const int maxw = sh_max_waves(p->dtype), G = kShG;
   // Wavefronts per workgroup: one, two or four workgroups share a CU's wavefront slots and its
   // LDS. More trials per workgroup share each sum, fewer keep windows short where delays
@@ -455,6 +455,8 @@ bool plan_shared(dd_plan* p, int64_t lds_cap) {
       double cost = 0;
       for (int q = f0; q < f1; q += 4)
         if (!bundle_quad(p, q, std::min(f1, q + 4), g * n, n, cap, &v, &cost)) return false;
+      // bundles of like pattern counts share a stage: its slowest row sets its time
+      std::stable_sort(v.begin(), v.end(), [](const Bundle& a, const Bundle& b) { return a.np < b.np; });
       for (size_t i = 0; i < v.size();) {
         // bundles that fit half the LDS share, within the block, as long as each wavefront has
         // at most one row to form
@@ -467,7 +469,7 @@ bool plan_shared(dd_plan* p, int64_t lds_cap) {
         tab.resize(at + (size_t)ints, 0);
         int32_t* rec = &tab[at];
         int64_t base = kShSpare, reach = 0;
-        int32_t rows = 0, packed = 0;
+        int32_t rows = 0;
         for (int l = 0; l < 64; ++l) rec[4 * l] = 64 * kShBlock;
         for (size_t q = 0; q < e - i; ++q) {
           const Bundle& b = v[i + q];
@@ -481,8 +483,7 @@ bool plan_shared(dd_plan* p, int64_t lds_cap) {
           h[0] = b.m | b.np << 8;
           h[4] = b.slot;
           h[8] = (int32_t)base;
-          rows += b.rows;
-          packed |= (int32_t)((uint32_t)b.rows << (8 * q));
+          for (int k = 0; k < b.rows; ++k) rec[4 * (kShLaneMap + rows++) + 1] = (int32_t)q | k << 8;
           reach = std::max<int64_t>(reach, 4 * ((int64_t)b.rows * sh_row_chunks(p->dtype) + 64) + 8 +
                                                (p->dtype == DD_U8 ? kShWords : 0));
           for (int w = 0; w < nw; ++w)
@@ -491,7 +492,6 @@ bool plan_shared(dd_plan* p, int64_t lds_cap) {
           base += b.bytes();
         }
         rec[4 * kShLaneRows + 3] = rows;
-        rec[4 * (kShLaneRows + 1) + 3] = packed;
         rec[4 * kShLaneReach + 3] = (int32_t)reach;
         for (int w = 0; w < nw; ++w)
           rec[kShFormInts + kShAddInts * w + kShAddInts - 1] = (int32_t)(e - i) << 1 | (e == v.size() ? 1 : 0);
@@ -585,8 +585,10 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
     t.cc = tuning->chan_stage;
     t.pw = tuning->producer_waves;
   }
-  // a plan without any choice of the caller's may run in the shared-sum form
-  const bool auto_form = form_req == DD_FORM_AUTO && !tiles_set;
+  // a plan without any choice of the caller's runs in the shared-sum form, except FP32 beams of
+  // few channels (kShMinChans)
+  const bool auto_form =
+      form_req == DD_FORM_AUTO && !tiles_set && !(in_dtype == DD_F32 && nchan < dd::kShMinChans);
   // 8-bit input takes the direct-read form unless the caller asks for another form or sets
   // an LDS-form tile field
   const bool direct = form_req == DD_FORM_DIRECT || (form_req == DD_FORM_AUTO && in_dtype == DD_U8 && !tiles_set);

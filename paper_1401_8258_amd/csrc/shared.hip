@@ -52,7 +52,8 @@ static_assert(kRowB == 1008, "the row offsets of the window reads are written ou
 
 struct ShParams {
   const void* in;
-  int64_t row_stride, nvalid, ring_len, win0;
+  int64_t row_stride, nvalid, win0;
+  uint32_t ring, limit;  // ring length (0: linear); samples of a row that may be loaded
   const int32_t* tab;
   float* out;
   double* part;
@@ -86,7 +87,7 @@ constexpr int kRawN = DT == DD_F32 ? 4 : 2;  // raw dwords a lane holds per chan
 // A row of one bundle, wave-uniform, and the raw samples it is formed from.
 template <int DT>
 struct Row {
-  int live, mn, slot, dst, row, first;  // mn: channels | patterns << 8; first: its codes' first lane
+  int live, slot, dst, row, first;      // bytes per pattern, LDS offset, row, its codes' first lane
   uint32_t sh;                          // per channel 2 bits: bytes its first sample lies past the dword
   uint32_t v[4][kRawN<DT>];
 };
@@ -102,70 +103,91 @@ struct Stage {
 __device__ __forceinline__ int lane_w(const Stage& f, int l) { return __builtin_amdgcn_readlane(f.meta.w, l); }
 __device__ __forceinline__ int stage_rows(const Stage& f) { return lane_w(f, dd::kShLaneRows); }
 
+// Window starts: sample wbase + offset of its channel, less ring_len past the ring's end (the
+// difference wraps to a large number before it; ring_len is 0 for linear input).
 template <int DT>
-__device__ __forceinline__ void open_stage(const ShParams& P, int64_t wbase, Stage& f) {
+__device__ __forceinline__ void open_stage(const ShParams& P, uint32_t wbase, Stage& f) {
   constexpr int EB = kEB<DT>;
-  int64_t s = wbase + f.meta.y;
-  if (P.ring_len > 0 && s >= P.ring_len) s -= P.ring_len;
-  f.start = (uint64_t)P.in + (uint64_t)(((int64_t)f.meta.z * P.row_stride + s) * EB);
+  const uint32_t s0 = wbase + (uint32_t)f.meta.y, s1 = s0 - P.ring;
+  const uint32_t s = s1 < s0 ? s1 : s0;
+  const uint64_t stride = (uint64_t)P.row_stride * EB;
+  const uint64_t at = (uint64_t)(uint32_t)f.meta.z * (uint32_t)stride + (uint64_t)P.in;
+  f.start = at + ((uint64_t)((uint32_t)f.meta.z * (uint32_t)(stride >> 32)) << 32) + (uint64_t)s * EB;
   const int reach = lane_w(f, dd::kShLaneReach);  // samples past its start a window may load
-  f.safe = __ballot(P.ring_len > 0 || s + reach <= P.nvalid);
+  f.safe = __ballot(s + (uint32_t)reach <= P.limit);
+}
+
+// This lane's dwords of one channel, from the scalar window start p and the lane's offset vo.
+template <int DT>
+__device__ __forceinline__ void load_words(gptr_t p, uint32_t vo, uint32_t (&v)[kRawN<DT>]) {
+  if constexpr (DT == DD_F32) {
+    const u4u_t q = *(const DD_GLOBAL u4u_t*)(p + vo);
+    v[0] = q.x, v[1] = q.y, v[2] = q.z, v[3] = q.w;
+  } else if constexpr (DT == DD_F16) {
+    const u2u_t q = *(const DD_GLOBAL u2u_t*)(p + vo);
+    v[0] = q.x, v[1] = q.y;
+  } else {
+    v[0] = *(const DD_GLOBAL uint32_t*)(p + vo);
+    v[1] = *(const DD_GLOBAL uint32_t*)(p + dd::kShWords + vo);
+  }
 }
 
 // Row t of the stage: its header, and its raw samples' loads: lane l of row r of a bundle loads
 // the 4 window positions 4 (r VC + l) .. + 3 of every channel (8-bit input: also those 1008
-// samples later), in whole dwords. Where a window would pass the last sample, each dword is
-// clamped to that of the last sample: positions past it are used by no stored output.
+// samples later), in whole dwords; channels the bundle lacks are zeros. Where a window would
+// pass the last sample, each dword is clamped to that of the last sample: positions past it
+// are used by no stored output. The usual case is one block of loads with scalar starts: a
+// choice per channel, or starts in vector registers, made the compiler wait for earlier loads
+// between them (54.2 -> XX ms on the full FP32 workload).
 template <int DT>
-__device__ __forceinline__ void load_row(const ShParams& P, const Stage& f, int t, int64_t wbase, int lane, Row<DT>& r) {
+__device__ __forceinline__ void load_row(const ShParams& P, const Stage& f, int t, int lane, Row<DT>& r) {
   constexpr int VC = dd::sh_row_chunks(DT);
   constexpr int EB = kEB<DT>;
   r.live = t < stage_rows(f);
   if (!r.live) return;
-  // bundle of row t: the rows of the four bundles are packed in bytes
-  const uint32_t rb = (uint32_t)lane_w(f, dd::kShLaneRows + 1);
-  int b = 0;
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    const int n = (int)((rb >> (8 * i)) & 255u);
-    if (b == i && t >= n) t -= n, b = i + 1;
-  }
-  r.mn = lane_w(f, 4 * b);
+  const int br = __builtin_amdgcn_readlane(f.meta.y, dd::kShLaneMap + t);  // bundle | row << 8
+  const int b = br & 255;
+  r.row = br >> 8;
   r.slot = lane_w(f, 4 * b + 1);
   r.dst = lane_w(f, 4 * b + 2);
-  r.row = t;
   r.first = 16 * b;
+  const int m = lane_w(f, 4 * b) & 255;
+  uint64_t start[4];
   r.sh = 0;
-  const uint32_t vo = (uint32_t)(t * VC + lane) * (4 * kDw<DT>);
-  const bool whole = ((f.safe >> (4 * b)) & 15) == 15;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int l = 4 * b + j;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)f.start, l);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(f.start >> 32), l);
-    const uint64_t a = (lo & ~3u) | (uint64_t)hi << 32;
-    const gptr_t p = (gptr_t)a;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)f.start, 4 * b + j);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(f.start >> 32), 4 * b + j);
+    start[j] = (lo & ~3u) | (uint64_t)hi << 32;
     if (DT != DD_F32) r.sh |= (lo & 3u) << (2 * j);
-    if (whole) {
-      if constexpr (DT == DD_F32) {
-        const u4u_t q = *(const DD_GLOBAL u4u_t*)(p + vo);
-        r.v[j][0] = q.x, r.v[j][1] = q.y, r.v[j][2] = q.z, r.v[j][3] = q.w;
-      } else if constexpr (DT == DD_F16) {
-        const u2u_t q = *(const DD_GLOBAL u2u_t*)(p + vo);
-        r.v[j][0] = q.x, r.v[j][1] = q.y;
-      } else {
-        r.v[j][0] = *(const DD_GLOBAL uint32_t*)(p + vo);
-        r.v[j][1] = *(const DD_GLOBAL uint32_t*)(p + dd::kShWords + vo);
-      }
-    } else {
-      // a window starts before the last sample of its channel, so lim is not negative
-      const uint64_t row =
-          (uint64_t)P.in + (uint64_t)((int64_t)__builtin_amdgcn_readlane(f.meta.z, l) * P.row_stride * EB);
-      const uint32_t lim = (uint32_t)(((row + (uint64_t)(P.nvalid * EB - 1)) & ~(uint64_t)3) - a);
+  }
+  uint32_t vo = (uint32_t)(r.row * VC + lane) * (4 * kDw<DT>);
+  const bool whole = ((f.safe >> (4 * b)) & 15) == 15;
+  if (whole && m == 4) {
 #pragma unroll
-      for (int i = 0; i < kRawN<DT>; ++i) {
-        const uint32_t o = vo + (DT == DD_U8 ? i * dd::kShWords : 4 * i);
-        r.v[j][i] = *(const DD_GLOBAL uint32_t*)(p + (o < lim ? o : lim));
+    for (int j = 0; j < 4; ++j) {
+      asm volatile("" : "+v"(vo));  // a 32-bit offset here, so that the load takes the scalar start
+      load_words<DT>((gptr_t)start[j], vo, r.v[j]);
+    }
+  } else {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      if (j >= m) {
+#pragma unroll
+        for (int i = 0; i < kRawN<DT>; ++i) r.v[j][i] = 0;
+      } else if (whole) {
+        asm volatile("" : "+v"(vo));
+        load_words<DT>((gptr_t)start[j], vo, r.v[j]);
+      } else {
+        // a window starts before the last sample of its channel, so lim is not negative
+        const uint64_t row = (uint64_t)P.in +
+                             (uint64_t)((int64_t)__builtin_amdgcn_readlane(f.meta.z, 4 * b + j) * P.row_stride * EB);
+        const uint32_t lim = (uint32_t)(((row + (uint64_t)(P.nvalid * EB - 1)) & ~(uint64_t)3) - start[j]);
+#pragma unroll
+        for (int i = 0; i < kRawN<DT>; ++i) {
+          const uint32_t o = vo + (DT == DD_U8 ? i * dd::kShWords : 4 * i);
+          r.v[j][i] = *(const DD_GLOBAL uint32_t*)((gptr_t)start[j] + (o < lim ? o : lim));
+        }
       }
     }
   }
@@ -258,7 +280,7 @@ __device__ __forceinline__ void form(const uint32_t (&w)[4][4], int codes, int i
   DD_FORM("v_add_u32");
 }
 
-// Forms row r: the words of its channels (zeros for those the bundle lacks), then the sums.
+// Forms row r: the words of its channels, then the sums.
 // Lanes without a window chunk of their own write to the spare slot.
 template <int DT>
 __device__ __forceinline__ void form_row(const Row<DT>& r, int codes, int lane, uint32_t lds, uint32_t spare) {
@@ -266,16 +288,10 @@ __device__ __forceinline__ void form_row(const Row<DT>& r, int codes, int lane, 
   constexpr int VC = dd::sh_row_chunks(DT);
   T w[4][4];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    words<DT>(r, j, w[j]);
-    if (j >= (r.mn & 255)) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) w[j][i] = T(0);
-    }
-  }
+  for (int j = 0; j < 4; ++j) words<DT>(r, j, w[j]);
   const int idx = r.row * VC + lane;
   const bool mine = lane < VC && idx * 16 < r.slot;
-  form(w, codes, r.first, mine ? lds + r.dst + 16 * idx : spare + 16 * lane, mine ? r.slot : 0);
+  form(w, codes, __builtin_amdgcn_readfirstlane(r.first), mine ? lds + r.dst + 16 * idx : spare + 16 * lane, mine ? r.slot : 0);
 }
 
 __device__ __forceinline__ void stage_barrier() {
@@ -295,7 +311,8 @@ __device__ __forceinline__ void stage_barrier() {
 #define DD_SH3(n, A0, A1, A2, A3, W0, W1, W2, W3) DD_OWN(n, A0, W3) DD_NEXT(n, A1, W0) DD_NEXT(n, A2, W1) DD_NEXT(n, A3, W2)
 // Row by row: wait for the row, add it, start the same row of the next unit's window.
 #define DD_WAIT "s_waitcnt lgkmcnt(3)\n\t"
-#define DD_ROWS(SH, n, A0, A1, A2, A3, A4, A5, A6, A7, A8, A9, A10, A11, A12, A13, A14, A15)             \
+#define DD_ROWS(SH, n, ...) DD_ROWS_(SH, n, __VA_ARGS__)
+#define DD_ROWS_(SH, n, A0, A1, A2, A3, A4, A5, A6, A7, A8, A9, A10, A11, A12, A13, A14, A15)             \
   DD_WAIT SH(n, A0, A1, A2, A3, 112, 113, 114, 115) "ds_read_b128 v[112:115], %[va]\n\t"                 \
   DD_WAIT SH(n, A4, A5, A6, A7, 116, 117, 118, 119) "ds_read_b128 v[116:119], %[va] offset:1008\n\t"     \
   DD_WAIT SH(n, A8, A9, A10, A11, 120, 121, 122, 123) "ds_read_b128 v[120:123], %[va] offset:2016\n\t"   \
@@ -304,8 +321,7 @@ __device__ __forceinline__ void stage_barrier() {
 // A register that a read in flight will fill is read only after the wait for it.
 #define DD_UNIT(n, K, ...)                      \
   "s_add_u32 %[i], %[i], 1\n\t"                 \
-  "s_min_u32 %[s1], %[i], %[n]\n\t"             \
-  "v_readlane_b32 %[s1], %[meta], %[s1]\n\t"    \
+  "v_readlane_b32 %[s1], %[meta], %[i]\n\t"     \
   "s_and_b32 %[s2], %[s1], -16\n\t"             \
   "v_add_u32 %[va], %[s2], %[base]\n\t"         \
   "s_cmp_lt_u32 %[s0], 2\n\t"                   \
@@ -326,10 +342,36 @@ __device__ __forceinline__ void stage_barrier() {
   DD_ROWS(DD_SH3, n, __VA_ARGS__)               \
   "Ldd_e" #K "_%=:\n\t"                         \
   "s_and_b32 %[s0], %[s1], 3\n\t"
+// The last unit: nothing left to read.
+#define DD_LAST_ROWS(SH, n, ...) DD_LAST_ROWS_(SH, n, __VA_ARGS__)
+#define DD_LAST_ROWS_(SH, n, A0, A1, A2, A3, A4, A5, A6, A7, A8, A9, A10, A11, A12, A13, A14, A15)      \
+  "s_waitcnt lgkmcnt(3)\n\t" SH(n, A0, A1, A2, A3, 112, 113, 114, 115)                                 \
+  "s_waitcnt lgkmcnt(2)\n\t" SH(n, A4, A5, A6, A7, 116, 117, 118, 119)                                 \
+  "s_waitcnt lgkmcnt(1)\n\t" SH(n, A8, A9, A10, A11, 120, 121, 122, 123)                               \
+  "s_waitcnt lgkmcnt(0)\n\t" SH(n, A12, A13, A14, A15, 124, 125, 126, 127)
+#define DD_LAST(n, ...)                         \
+  "Ldd_last_%=:\n\t"                            \
+  "s_cmp_lt_u32 %[s0], 2\n\t"                   \
+  "s_cbranch_scc0 Ldd_lc_%=\n\t"                \
+  "s_cmp_eq_u32 %[s0], 0\n\t"                   \
+  "s_cbranch_scc0 Ldd_lb_%=\n\t"                \
+  DD_LAST_ROWS(DD_SH0, n, __VA_ARGS__)          \
+  "s_branch Ldd_le_%=\n"                        \
+  "Ldd_lb_%=:\n\t"                              \
+  DD_LAST_ROWS(DD_SH1, n, __VA_ARGS__)          \
+  "s_branch Ldd_le_%=\n"                        \
+  "Ldd_lc_%=:\n\t"                              \
+  "s_cmp_eq_u32 %[s0], 2\n\t"                   \
+  "s_cbranch_scc0 Ldd_ld_%=\n\t"                \
+  DD_LAST_ROWS(DD_SH2, n, __VA_ARGS__)          \
+  "s_branch Ldd_le_%=\n"                        \
+  "Ldd_ld_%=:\n\t"                              \
+  DD_LAST_ROWS(DD_SH3, n, __VA_ARGS__)          \
+  "Ldd_le_%=:"
 // A stage's bundles: units (bundle, trial) in order, meta lane `unit` holding the window's
 // LDS byte offset and shift; n is the last unit. All of the window registers' reads end in
 // here: one asm block, so that nothing else touches them while a read is in flight.
-#define DD_STAGE_IN                                 \
+#define DD_STAGE(n)                                 \
   "s_mov_b32 %[i], 0\n\t"                           \
   "v_readlane_b32 %[s1], %[meta], 0\n\t"            \
   "s_and_b32 %[s2], %[s1], -16\n\t"                 \
@@ -339,11 +381,13 @@ __device__ __forceinline__ void stage_barrier() {
   "ds_read_b128 v[116:119], %[va] offset:1008\n\t"  \
   "ds_read_b128 v[120:123], %[va] offset:2016\n\t"  \
   "ds_read_b128 v[124:127], %[va] offset:3024\n"    \
-  "Ldd_l_%=:\n\t"
-#define DD_STAGE_OUT                                \
-  "s_cmp_le_u32 %[i], %[n]\n\t"                     \
-  "s_cbranch_scc1 Ldd_l_%=\n\t"                     \
-  "s_waitcnt lgkmcnt(0)"
+  "Ldd_l_%=:\n\t"                                   \
+  DD_UNIT(n, 0, DD_U0)                              \
+  "s_cmp_ge_u32 %[i], %[n]\n\t"                     \
+  "s_cbranch_scc1 Ldd_last_%=\n\t"                  \
+  DD_UNIT(n, 1, DD_U1)                              \
+  "s_branch Ldd_l_%=\n"                             \
+  DD_LAST(n, DD_U1)
 #define DD_ACC(g)                                                                                          \
   "+v"(acc[g][0]), "+v"(acc[g][1]), "+v"(acc[g][2]), "+v"(acc[g][3]), "+v"(acc[g][4]), "+v"(acc[g][5]),    \
       "+v"(acc[g][6]), "+v"(acc[g][7]), "+v"(acc[g][8]), "+v"(acc[g][9]), "+v"(acc[g][10]),                \
@@ -354,29 +398,26 @@ __device__ __forceinline__ void stage_barrier() {
   "scc", "memory", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", \
       "v123", "v124", "v125", "v126", "v127"
 
-__device__ __forceinline__ void add_stage(float (&acc)[dd::kShG][16], int meta, uint32_t base, int n) {
+#define DD_U0 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15
+#define DD_U1 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31
+static_assert(dd::kShG == 2, "the stage's code walks two trials");
+__device__ __forceinline__ void add_stage(float (&acc)[2][16], int meta, uint32_t base, int n) {
   uint32_t va, i, s0, s1, s2;
-  asm volatile(DD_STAGE_IN
-               DD_UNIT("v_add_f32", 0, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15)
-               DD_UNIT("v_add_f32", 1, 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31)
-               DD_STAGE_OUT
+  asm volatile(DD_STAGE("v_add_f32")
                : DD_ACC(0), DD_ACC(1), DD_STAGE_TMP
                : DD_STAGE_USE
                : DD_STAGE_CLOBBER);
 }
-__device__ __forceinline__ void add_stage(uint32_t (&acc)[dd::kShG][16], int meta, uint32_t base, int n) {
+__device__ __forceinline__ void add_stage(uint32_t (&acc)[2][16], int meta, uint32_t base, int n) {
   uint32_t va, i, s0, s1, s2;
-  asm volatile(DD_STAGE_IN
-               DD_UNIT("v_add_u32", 0, 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15)
-               DD_UNIT("v_add_u32", 1, 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31)
-               DD_STAGE_OUT
+  asm volatile(DD_STAGE("v_add_u32")
                : DD_ACC(0), DD_ACC(1), DD_STAGE_TMP
                : DD_STAGE_USE
                : DD_STAGE_CLOBBER);
 }
 
-// Blocks of DD_CHAN_BLOCK channels (FP32) or 256 channels (8-bit codes: 255 x 256 < 2^16)
-// close into the running totals.
+// Blocks of kShFold channels (FP32) or 256 channels (8-bit codes: 255 x 256 < 2^16) close into
+// the running totals.
 __device__ __forceinline__ void fold(float (&tot)[16], float (&acc)[16]) {
 #pragma unroll
   for (int i = 0; i < 16; ++i) {
@@ -414,8 +455,7 @@ __device__ __forceinline__ void unit(const ShParams& P, int64_t tile, int grp, c
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   ci32_t tab = (ci32_t)P.tab;
   const int nst = tab[2 * grp + 1];
-  int64_t wbase = P.win0 + t0;
-  if (P.ring_len > 0) wbase %= P.ring_len;
+  const uint32_t wbase = (uint32_t)(P.ring ? (P.win0 + t0) % P.ring : t0);
   const uint32_t lds = dd::lds_addr(smem);
   const uint32_t spare = lds;
   const uint32_t base = lds + 16 * lane;
@@ -425,45 +465,58 @@ __device__ __forceinline__ void unit(const ShParams& P, int64_t tile, int grp, c
   const DD_GLOBAL int32_t* rec = (const DD_GLOBAL int32_t*)P.tab + tab[2 * grp];
   const int at_add = dd::kShFormInts + dd::kShAddInts * wv + (lane & (dd::kShAddInts - 1));
 
-  // Iteration s adds stage s (from s = 0) and forms stage s + 1, whose first row of raw samples
-  // per wavefront was loaded in iteration s - 1.
-  Stage cur, nxt;
+  // Every wavefront alternates adding a stage with forming the next one. Between two barriers
+  // the two are independent; half of a SIMD's wavefronts form first (their barrier comes
+  // between the adds and the forming, one stage further on), so that the LDS reads of some run
+  // beside the LDS writes of others. The first row of a stage's raw samples is loaded when the
+  // stage before has been formed.
+  const bool form_first = (wv >> 2) & 1;
+  // Loads return in order, so what an iteration needs beside the raw samples (the next record
+  // to form from, the next offsets) is loaded at its start and waited on before the next raw
+  // loads go out.
+  const DD_GLOBAL int32_t* arec = rec + at_add;
+  int offs = *arec;
+  Stage cur;  // the stage to form
   cur.meta = *(const DD_GLOBAL i4_t*)(rec + 4 * lane);
+  asm volatile("" : "+v"(offs), "+v"(cur.meta));
   open_stage<DT>(P, wbase, cur);
   Row<DT> r;
-  load_row<DT>(P, cur, wv, wbase, lane, r);
-  int offs = 0, noffs = rec[at_add];
-  if (nst > 1) rec += ints;
-  nxt.meta = *(const DD_GLOBAL i4_t*)(rec + 4 * lane);
-  int s = -1;
+  load_row<DT>(P, cur, wv, lane, r);
+  int formed = 0;
+  int s = form_first ? -2 : -1;
   asm volatile("" : "+s"(s));  // one copy of the loop body: no peeled first iteration
 #pragma nounroll
   for (; s < nst; ++s) {
-    // cur: stage s + 1; nxt: stage s + 2, whose record rec points at
+    const int now = offs;
+    if (s >= 0 && s + 1 < nst) arec += ints;
+    offs = *arec;
+    if (formed + 1 < nst) rec += ints;
+    const i4_t next = *(const DD_GLOBAL i4_t*)(rec + 4 * lane);  // the stage after cur
     if (s >= 0) {
-      const int flags = __builtin_amdgcn_readlane(offs, dd::kShAddInts - 1);  // bundles << 1 | fold
-      add_stage(acc, offs, base, G * (flags >> 1) - 1);
+      const int flags = __builtin_amdgcn_readlane(now, dd::kShAddInts - 1);  // bundles << 1 | fold
+      add_stage(acc, now, base, __builtin_amdgcn_readfirstlane(G * (flags >> 1) - 1));
       if (flags & 1) {
 #pragma unroll
         for (int g = 0; g < G; ++g) fold(tot[g], acc[g]);
       }
     }
-    if (s + 1 < nst) {
+    if (form_first && s >= -1) stage_barrier();
+    if (formed < nst) {
       const int rows = stage_rows(cur);
       if (r.live) form_row<DT>(r, cur.meta.x, lane, lds, spare);
       for (int t = wv + P.nw; t < rows; t += P.nw) {
-        load_row<DT>(P, cur, t, wbase, lane, r);
+        load_row<DT>(P, cur, t, lane, r);
         form_row<DT>(r, cur.meta.x, lane, lds, spare);
       }
-      cur = nxt;
-      offs = noffs;
-      noffs = rec[at_add];
-      if (s + 3 < nst) rec += ints;
-      nxt.meta = *(const DD_GLOBAL i4_t*)(rec + 4 * lane);
-      open_stage<DT>(P, wbase, cur);
-      if (s + 2 < nst) load_row<DT>(P, cur, wv, wbase, lane, r);
+      ++formed;
     }
-    stage_barrier();
+    cur.meta = next;
+    asm volatile("" : "+v"(offs), "+v"(cur.meta));
+    if (formed < nst) {
+      open_stage<DT>(P, wbase, cur);
+      load_row<DT>(P, cur, wv, lane, r);
+    }
+    if (!form_first) stage_barrier();
   }
 
   // outputs, and FP64 sums of the tile's outputs per trial (a fixed tree)
@@ -536,8 +589,10 @@ int launch_shared(const dd_plan* p, const InView& in, const int32_t* d_table, in
   P.in = in.ptr;
   P.row_stride = in.row_stride;
   P.nvalid = in.nvalid;
-  P.ring_len = in.ring_len;
   P.win0 = in.win0;
+  P.ring = (uint32_t)in.ring_len;
+  // a ring row goes on past its length far enough for every window
+  P.limit = in.ring_len > 0 ? 0x7fffffffu : (uint32_t)in.nvalid;
   P.tab = d_table;
   P.out = out;
   P.part = part;

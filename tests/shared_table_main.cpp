@@ -34,9 +34,10 @@ static int check(const dd_plan* p) {
         for (int k = 0; k <= dd::kShMaxPat; ++k) code[k] = rec[4 * (16 * q + k)];
         if (m < 1 || m > 4 || np < 1 || np > dd::kShMaxPat || slot % 16 || base % 16 || base < dd::kShSpare) return 5;
         if ((int64_t)base + (int64_t)np * slot > p->sh.lds) return 6;
-        const int nrow = (rec[4 * (dd::kShLaneRows + 1) + 3] >> (8 * q)) & 255;
-        if (nrow != (slot / 16 + vc - 1) / vc) return 7;
-        rows += nrow;
+        const int nrow = (slot / 16 + vc - 1) / vc;
+        if (rows + nrow > dd::kShMaxRows) return 7;
+        for (int k = 0; k < nrow; ++k)
+          if (rec[4 * (dd::kShLaneMap + rows++) + 1] != (q | k << 8)) return 7;
         lo = std::min<int64_t>(lo, base), hi = std::max<int64_t>(hi, (int64_t)base + (int64_t)np * slot);
         // raw samples a lane may load past the window start
         const int64_t reach = 4 * ((int64_t)(nrow - 1) * vc + 63) + 8 + (p->dtype == DD_U8 ? dd::kShWords : 0);
@@ -70,7 +71,7 @@ static int check(const dd_plan* p) {
       if (rows != rec[4 * dd::kShLaneRows + 3]) return 16;
       if (s > 0 && lo < prev_hi && prev_lo < hi) return 17;  // written while the stage before is read
       prev_lo = lo, prev_hi = hi;
-      if (open > (p->dtype == DD_U8 ? 256 : DD_CHAN_BLOCK)) return 18;
+      if (open > (p->dtype == DD_U8 ? 256 : dd::kShFold)) return 18;
       if (fold) open = 0;
       else if (s + 1 == nst) return 19;  // the last stage folds
     }
