@@ -81,24 +81,25 @@ constexpr int kShFold = 128;
 // 14 patterns per 16 to 32 trials at 64 channels, 4 at 1024), and their series stay those of
 // every explicit tiling, bit for bit.
 constexpr int kShMinChans = 128;
-constexpr int kShMaxBundles = 4;  // bundles of a stage
+constexpr int kShMaxBundles = 3;  // bundles of a stage
 constexpr int kShBlock = 132;     // bytes of code per pattern block
 constexpr int kShSpare = 1024;    // LDS bytes before the stages: where lanes without a chunk write
-// A stage's record. Lane l's four ints, for forming: x the code offset of pattern l % 16 of
-// bundle l / 16 (pattern * kShBlock; past the last one 64 * kShBlock); y, z the window start
-// and the channel of (bundle, channel) l (lanes 0-15); w per bundle {channels | patterns << 8,
-// bytes per pattern, LDS offset, 0} at 4 b, the stage's rows at kShLaneRows, and the samples
-// past a window's start that a row may load at kShLaneReach; y from kShLaneMap on the stage's
-// rows, bundle | row of the bundle << 8. Then per wavefront kShAddInts ints, for adding: its trials' LDS offsets (byte
-// offset of the window's 16-byte boundary | words past it) in bundle order, and in the last
-// int bundles << 1 | fold.
-constexpr int kShFormInts = 256;
-constexpr int kShAddInts = 16;
-constexpr int kShLaneRows = 16;
-constexpr int kShLaneReach = 17;
-constexpr int kShLaneMap = 16;
-constexpr int kShMaxRows = 48;  // rows of a stage
+// A stage's record, for forming: four ints per lane, 16 lanes per bundle b. x of lane 16 b + i:
+// the code offset of its pattern i (pattern * kShBlock; past the last one 64 * kShBlock); y and
+// z of lane 16 b + j: its channel j's window start and index; w of lanes 16 b, + 1, + 2: its
+// channels, bytes per pattern and LDS offset; w of the lanes below, for the stage: its rows, the
+// rows up to bundles 0, 1 and 2 in bytes, and the samples past a window's start that a row may
+// load. Then per wavefront kShAddInts ints, for adding: its trials' LDS offsets (byte offset of
+// the window's 16-byte boundary | words past it) in bundle order, and in the last int
+// bundles << 1 | fold.
+constexpr int kShFormInts = 4 * 16 * kShMaxBundles;
+constexpr int kShAddInts = 8;
+constexpr int kShLaneRows = 3;
+constexpr int kShLaneEnds = 4;
+constexpr int kShLaneReach = 5;
+constexpr int kShMaxRows = 80;  // rows of a bundle (of a stage: a byte)
 constexpr int sh_stage_ints(int nw) { return kShFormInts + kShAddInts * nw; }
+static_assert(kShG * kShMaxBundles < kShAddInts, "a wavefront's offsets and flags fit its ints");
 struct Shared {
   bool on = false;
   int32_t nw = 0;      // wavefronts per workgroup

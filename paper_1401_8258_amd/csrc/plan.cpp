@@ -310,70 +310,80 @@ int plan_direct(dd_plan* p, const Tiles& t) {
 
 namespace {
 
+constexpr int kShMaxTrials = 2 * 16;  // trials of a group
+
 // One bundle of 1..4 consecutive channels for one group of trials.
 struct Bundle {
-  int m = 0, np = 0, slot = 0, rows = 0;  // channels, patterns, bytes of a pattern's sums, rows
-  int32_t off[4] = {0, 0, 0, 0}, ch[4] = {0, 0, 0, 0};
-  uint8_t code[kShMaxPat] = {0};
-  std::vector<int32_t> trial;  // byte offset from the bundle's LDS base | words past 16 bytes
+  int m, np, slot, rows;  // channels, patterns, bytes of a pattern's sums, rows
+  int32_t off[4], ch[4];
+  uint8_t code[kShMaxPat];
+  int32_t trial[kShMaxTrials];  // byte offset from the bundle's LDS base | words past 16 bytes
   int64_t bytes() const { return (int64_t)np * slot; }
-  double cost = 0;
+  double cost;
 };
 
-// Clocks of one CU: four 1 KB LDS reads per trial at 221 B/clk, and the sums' writes at 128
-// B/clk (both measured rates).
-constexpr double kShReadClk = 4 * 1024 / 221.0;
+// Clocks of one CU with all its wavefronts at work (measured): a trial's sum of one bundle
+// added, a pattern's sums of one row formed, and what a row takes besides.
+constexpr double kShAddClk = 26.0;
+constexpr double kShPatClk = 21.0;
+constexpr double kShRowClk = 60.0;
 
 // Channels c0 .. c0 + m - 1 for trials d0 .. d0 + n - 1 (past the last trial: the last one).
 // The reference channel is the bundle's smallest delay, so every relative delay is >= 0.
 // False when the patterns are too many or too wide, or the sums take more than cap bytes.
 bool make_bundle(const dd_plan* p, int c0, int m, int d0, int n, int64_t cap, Bundle* b) {
   const int32_t ndm = p->ndm;
-  const int dl = std::min(d0 + n, (int)ndm) - 1;
+  const int nd = std::min(n, (int)ndm - d0);  // trials of the group's own
   const int32_t* row[4];
   int ref = 0;
   for (int j = 0; j < m; ++j) {
-    row[j] = &p->delays[(size_t)(c0 + j) * ndm];
-    if (row[j][dl] < row[ref][dl]) ref = j;
+    row[j] = &p->delays[(size_t)(c0 + j) * ndm + d0];
+    if (row[j][nd - 1] < row[ref][nd - 1]) ref = j;
   }
   std::swap(row[0], row[ref]);
+  const int32_t k0 = row[0][0];
+  const int64_t chunks = (int64_t)(row[0][nd - 1] - k0) / 4 + 4 * 63 + 1;
+  if (16 * chunks > cap) return false;
   b->m = m;
-  for (int j = 0; j < m; ++j) b->ch[j] = c0 + j;
-  std::swap(b->ch[0], b->ch[ref]);
-  int32_t lo[4] = {0, 0, 0, 0}, hi[4] = {0, 0, 0, 0};
-  for (int j = 1; j < m; ++j) {
-    lo[j] = hi[j] = row[j][d0] - row[0][d0];
-    for (int d = d0 + 1; d <= dl; ++d) {
-      const int32_t r = row[j][d] - row[0][d];
-      lo[j] = std::min(lo[j], r);
-      hi[j] = std::max(hi[j], r);
-    }
-    if (hi[j] - lo[j] > kShMaxE || lo[j] < 0) return false;
-  }
-  const int32_t k0 = row[0][d0];
-  const int64_t chunks = (int64_t)(row[0][dl] - k0) / 4 + 4 * 63 + 1;
-  b->slot = (int)std::min<int64_t>(16 * chunks, 1 << 24);
+  b->slot = (int)(16 * chunks);
   b->rows = (int)((chunks + sh_row_chunks(p->dtype) - 1) / sh_row_chunks(p->dtype));
-  if ((int64_t)b->slot > cap || b->rows > kShMaxRows) return false;
-  for (int j = 0; j < m; ++j) b->off[j] = k0 + lo[j];
-  int8_t slot_of[256];
+  if (b->rows > kShMaxRows) return false;
+  int32_t code[kShMaxTrials] = {0};
+  b->off[0] = k0;
+  for (int j = 0; j < 4; ++j) b->ch[j] = c0 + (j < m ? j : 0);
+  std::swap(b->ch[0], b->ch[ref]);
+  for (int j = 1; j < m; ++j) {
+    int32_t rel[kShMaxTrials], lo, hi;
+    const int32_t *rj = row[j], *r0 = row[0];
+    lo = hi = rj[0] - r0[0];
+    for (int t = 0; t < nd; ++t) {
+      const int32_t r = rj[t] - r0[t];
+      rel[t] = r;
+      lo = r < lo ? r : lo;
+      hi = r > hi ? r : hi;
+    }
+    if (hi - lo > kShMaxE || lo < 0) return false;
+    b->off[j] = k0 + lo;
+    for (int t = 0; t < nd; ++t) code[t] |= (rel[t] - lo) << (2 * (j - 1));
+  }
+  // channels the bundle lacks repeat its first one (their samples are not used)
+  for (int j = m; j < 4; ++j) b->off[j] = b->off[0], b->ch[j] = b->ch[0];
+  int8_t slot_of[64];
   std::memset(slot_of, -1, sizeof(slot_of));
   b->np = 0;
-  b->trial.resize((size_t)n);
-  for (int t = 0; t < n; ++t) {
-    const int d = std::min(d0 + t, dl);
-    uint32_t c = 0;
-    for (int j = 1; j < m; ++j) c |= (uint32_t)(row[j][d] - row[0][d] - lo[j]) << (2 * j);
+  for (int t = 0; t < nd; ++t) {
+    const int c = code[t];
     if (slot_of[c] < 0) {
       if (b->np == kShMaxPat) return false;
       slot_of[c] = (int8_t)b->np;
-      b->code[b->np++] = (uint8_t)(c >> 2);  // the reference channel has no shift
+      b->code[b->np++] = (uint8_t)c;
     }
-    const int32_t k = row[0][d] - k0;
-    b->trial[(size_t)t] = slot_of[c] * b->slot + (k & ~3) * 4 + (k & 3);
+    const int32_t k = row[0][t] - k0;
+    b->trial[t] = slot_of[c] * b->slot + (k & ~3) * 4 + (k & 3);
   }
   if (b->bytes() > cap) return false;
-  b->cost = n * kShReadClk + (double)b->bytes() / 128.0;
+  for (int t = nd; t < n; ++t) b->trial[t] = b->trial[nd - 1];
+  b->cost = n * kShAddClk + b->rows * (b->np * kShPatClk + kShRowClk);
   return true;
 }
 
@@ -381,27 +391,34 @@ bool make_bundle(const dd_plan* p, int c0, int m, int d0, int n, int64_t cap, Bu
 // cheaper or the whole does not fit. False when even single channels do not fit.
 bool bundle_quad(const dd_plan* p, int c0, int c1, int d0, int n, int64_t cap, std::vector<Bundle>* out, double* cost) {
   const int m = c1 - c0;
-  Bundle b;
-  const bool whole = m != 3 && make_bundle(p, c0, m, d0, n, cap, &b);
-  // a bundle of half the channels reads as much per trial: halves can only pay when the
-  // whole writes more than it saves
-  if (whole && (m == 1 || (double)b.bytes() / 128.0 <= n * kShReadClk)) {
-    out->push_back(std::move(b));
-    *cost += out->back().cost;
-    return true;
+  const size_t at = out->size();
+  out->resize(at + 1);
+  const bool whole = m != 3 && make_bundle(p, c0, m, d0, n, cap, &(*out)[at]);
+  // a bundle of half the channels adds as much per trial: halves can only pay when the whole
+  // forms more than that
+  if (whole) {
+    const double c = (*out)[at].cost;
+    if (m == 1 || c <= 2 * (n * kShAddClk + (*out)[at].rows * (kShPatClk + kShRowClk))) {
+      *cost += c;
+      return true;
+    }
+  } else {
+    out->pop_back();
+    if (m == 1) return false;
   }
-  if (m == 1) return false;
-  std::vector<Bundle> h;
+  const int mid = c0 + (m >= 3 ? 2 : 1);
   double hc = 0;
-  const int mid = c0 + (m == 4 ? 2 : m == 3 ? 2 : 1);
-  const bool halves = bundle_quad(p, c0, mid, d0, n, cap, &h, &hc) && bundle_quad(p, mid, c1, d0, n, cap, &h, &hc);
-  if (whole && (!halves || b.cost <= hc)) {
-    out->push_back(std::move(b));
-    *cost += out->back().cost;
+  const bool halves = bundle_quad(p, c0, mid, d0, n, cap, out, &hc) && bundle_quad(p, mid, c1, d0, n, cap, out, &hc);
+  if (whole && (!halves || (*out)[at].cost <= hc)) {
+    out->resize(at + 1);
+    *cost += (*out)[at].cost;
     return true;
   }
-  if (!halves) return false;
-  for (Bundle& x : h) out->push_back(std::move(x));
+  if (!halves) {
+    out->resize(at);
+    return false;
+  }
+  if (whole) out->erase(out->begin() + (std::ptrdiff_t)at);
   *cost += hc;
   return true;
 }
@@ -419,6 +436,7 @@ bool plan_shared(dd_plan* p, int64_t lds_cap) {
   // groups and channels wins.
   int best_div = 0;
   double best = 0;
+  std::vector<Bundle> v;
   for (int div = 1; div <= 4; div *= 2) {
     const int n = G * (maxw / div);
     if (div < 4 && ndm <= n / 2) continue;  // half the workgroup or more would be padding
@@ -430,7 +448,7 @@ bool plan_shared(dd_plan* p, int64_t lds_cap) {
     bool ok = true;
     for (int g = ng - 1; g >= 0 && ok; g -= gs)
       for (int q = nq - 1; q >= 0 && ok; q -= qs) {
-        std::vector<Bundle> v;
+        v.clear();
         ok = bundle_quad(p, 4 * q, std::min(nchan, 4 * q + 4), g * n, n, cap, &v, &cost);
         ++cnt;
       }
@@ -442,59 +460,68 @@ bool plan_shared(dd_plan* p, int64_t lds_cap) {
   const int nw = maxw / best_div, n = G * nw;
   const int64_t cap = (lds_cap / best_div - kShSpare) / 2 / 256 * 256;
   const int ng = (ndm + n - 1) / n;
-  const int ints = sh_stage_ints(nw);
+  const int form_ints = kShFormInts, ints = form_ints + kShAddInts * nw;
   std::vector<int32_t> tab((size_t)(2 * ng + 63) / 64 * 64, 0);
   int64_t max_stage = 0, max_reach = 0;
+  std::vector<int> order;
   std::vector<std::pair<size_t, int>> odd;  // records of odd stages and their bundles
   for (int g = 0; g < ng; ++g) {
     const size_t first = tab.size();
     int nst = 0;
     for (int f0 = 0; f0 < nchan; f0 += fold) {
       const int f1 = std::min(nchan, f0 + fold);
-      std::vector<Bundle> v;
+      v.clear();
       double cost = 0;
       for (int q = f0; q < f1; q += 4)
         if (!bundle_quad(p, q, std::min(f1, q + 4), g * n, n, cap, &v, &cost)) return false;
       // bundles of like pattern counts share a stage: its slowest row sets its time
-      std::stable_sort(v.begin(), v.end(), [](const Bundle& a, const Bundle& b) { return a.np < b.np; });
+      order.resize(v.size());
+      for (size_t i = 0; i < v.size(); ++i) order[i] = (int)i;
+      std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return v[(size_t)a].np < v[(size_t)b].np; });
+      auto at_rank = [&](size_t i) -> const Bundle& { return v[(size_t)order[i]]; };
       for (size_t i = 0; i < v.size();) {
-        // bundles that fit half the LDS share, within the block, as long as each wavefront has
-        // at most one row to form
+        // up to kShMaxBundles bundles that fit half the LDS share: as many as leave the fewest
+        // wavefronts without a row in the last round of rows
         size_t e = i + 1;
-        int64_t bytes = v[i].bytes();
-        int srows = v[i].rows;
-        while (e < v.size() && e - i < (size_t)kShMaxBundles && bytes + v[e].bytes() <= cap && srows + v[e].rows <= nw)
-          bytes += v[e].bytes(), srows += v[e++].rows;
+        int64_t bytes = at_rank(i).bytes();
+        int srows = at_rank(i).rows;
+        double best_fill = 0;
+        for (size_t k = i + 1;; ++k) {
+          const double fill = (double)srows / ((srows + nw - 1) / nw * nw);
+          if (fill >= best_fill) best_fill = fill, e = k;
+          if (k >= v.size() || k - i >= (size_t)kShMaxBundles) break;
+          bytes += at_rank(k).bytes();
+          srows += at_rank(k).rows;
+          if (bytes > cap || srows > 250) break;
+        }
         const size_t at = tab.size();
         tab.resize(at + (size_t)ints, 0);
         int32_t* rec = &tab[at];
         int64_t base = kShSpare, reach = 0;
-        int32_t rows = 0;
-        for (int l = 0; l < 64; ++l) rec[4 * l] = 64 * kShBlock;
+        int32_t rows = 0, ends = 0;
         for (size_t q = 0; q < e - i; ++q) {
-          const Bundle& b = v[i + q];
-          for (int j = 0; j < 4; ++j) {
-            // channels the bundle lacks repeat its first one (their samples are not used)
-            rec[4 * (4 * q + j) + 1] = b.off[j < b.m ? j : 0];
-            rec[4 * (4 * q + j) + 2] = b.ch[j < b.m ? j : 0];
-          }
-          for (int k = 0; k < b.np; ++k) rec[4 * (16 * q + k)] = b.code[k] * kShBlock;
-          int32_t* h = rec + 16 * q + 3;
-          h[0] = b.m | b.np << 8;
-          h[4] = b.slot;
-          h[8] = (int32_t)base;
-          for (int k = 0; k < b.rows; ++k) rec[4 * (kShLaneMap + rows++) + 1] = (int32_t)q | k << 8;
+          const Bundle& b = at_rank(i + q);
+          int32_t* l = rec + 64 * q;  // the bundle's 16 lanes
+          for (int k = 0; k < 16; ++k) l[4 * k] = (k < b.np ? b.code[k] : 64) * kShBlock;
+          for (int j = 0; j < 4; ++j) l[4 * j + 1] = b.off[j], l[4 * j + 2] = b.ch[j];
+          l[3] = b.m;
+          l[7] = b.slot;
+          l[11] = (int32_t)base;
+          rows += b.rows;
+          if (q < 3) ends |= (int32_t)((uint32_t)rows << (8 * q));
           reach = std::max<int64_t>(reach, 4 * ((int64_t)b.rows * sh_row_chunks(p->dtype) + 64) + 8 +
                                                (p->dtype == DD_U8 ? kShWords : 0));
           for (int w = 0; w < nw; ++w)
             for (int t = 0; t < G; ++t)
-              rec[kShFormInts + kShAddInts * w + G * (int)q + t] = (int32_t)base + b.trial[(size_t)(G * w + t)];
+              rec[form_ints + kShAddInts * w + G * (int)q + t] = (int32_t)base + b.trial[G * w + t];
           base += b.bytes();
         }
+        for (int q = (int)(e - i); q < 3; ++q) ends |= (int32_t)((uint32_t)0xFF << (8 * q));
         rec[4 * kShLaneRows + 3] = rows;
+        rec[4 * kShLaneEnds + 3] = ends;
         rec[4 * kShLaneReach + 3] = (int32_t)reach;
         for (int w = 0; w < nw; ++w)
-          rec[kShFormInts + kShAddInts * w + kShAddInts - 1] = (int32_t)(e - i) << 1 | (e == v.size() ? 1 : 0);
+          rec[form_ints + kShAddInts * w + kShAddInts - 1] = (int32_t)(e - i) << 1 | (e == v.size() ? 1 : 0);
         base -= kShSpare;
         max_stage = std::max(max_stage, base);
         max_reach = std::max(max_reach, reach);
@@ -510,9 +537,9 @@ bool plan_shared(dd_plan* p, int64_t lds_cap) {
   // odd stages use the second half of the LDS
   for (const auto& o : odd) {
     int32_t* rec = &tab[o.first];
-    for (int q = 0; q < o.second; ++q) rec[4 * (4 * q + 2) + 3] += (int32_t)max_stage;
+    for (int q = 0; q < o.second; ++q) rec[64 * q + 11] += (int32_t)max_stage;
     for (int w = 0; w < nw; ++w)
-      for (int t = 0; t < G * o.second; ++t) rec[kShFormInts + kShAddInts * w + t] += (int32_t)max_stage;
+      for (int t = 0; t < G * o.second; ++t) rec[form_ints + kShAddInts * w + t] += (int32_t)max_stage;
   }
   p->sh.on = true;
   p->sh.nw = nw;

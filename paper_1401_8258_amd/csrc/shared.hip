@@ -92,8 +92,8 @@ struct Row {
   uint32_t v[4][kRawN<DT>];
 };
 
-// A stage's record (lane l: four ints, dd_internal.h) and its window starts: lanes 0-15 hold
-// one per (bundle, channel).
+// A stage's record (lane l: four ints, dd_internal.h) and its window starts: lane 16 b + j
+// holds channel j's of bundle b.
 struct Stage {
   i4_t meta;
   uint64_t start;
@@ -145,24 +145,27 @@ __device__ __forceinline__ void load_row(const ShParams& P, const Stage& f, int 
   constexpr int EB = kEB<DT>;
   r.live = t < stage_rows(f);
   if (!r.live) return;
-  const int br = __builtin_amdgcn_readlane(f.meta.y, dd::kShLaneMap + t);  // bundle | row << 8
-  const int b = br & 255;
-  r.row = br >> 8;
-  r.slot = lane_w(f, 4 * b + 1);
-  r.dst = lane_w(f, 4 * b + 2);
-  r.first = 16 * b;
-  const int m = lane_w(f, 4 * b) & 255;
+  // the row's bundle, by the rows up to each (bytes; 255 past the last bundle)
+  const int ends = lane_w(f, dd::kShLaneEnds);
+  const int b = (t >= (ends & 255)) + (t >= ((ends >> 8) & 255));
+  static_assert(dd::kShMaxBundles == 3, "two ends tell three bundles apart");
+  const int first = 16 * b;
+  r.row = b ? t - ((ends >> (8 * b - 8)) & 255) : t;
+  r.slot = lane_w(f, first + 1);
+  r.dst = lane_w(f, first + 2);
+  r.first = first;
+  const int m = lane_w(f, first);
   uint64_t start[4];
   r.sh = 0;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)f.start, 4 * b + j);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(f.start >> 32), 4 * b + j);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)f.start, first + j);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(f.start >> 32), first + j);
     start[j] = (lo & ~3u) | (uint64_t)hi << 32;
     if (DT != DD_F32) r.sh |= (lo & 3u) << (2 * j);
   }
   uint32_t vo = (uint32_t)(r.row * VC + lane) * (4 * kDw<DT>);
-  const bool whole = ((f.safe >> (4 * b)) & 15) == 15;
+  const bool whole = ((f.safe >> first) & 15) == 15;
   if (whole && m == 4) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
@@ -181,7 +184,7 @@ __device__ __forceinline__ void load_row(const ShParams& P, const Stage& f, int 
       } else {
         // a window starts before the last sample of its channel, so lim is not negative
         const uint64_t row = (uint64_t)P.in +
-                             (uint64_t)((int64_t)__builtin_amdgcn_readlane(f.meta.z, 4 * b + j) * P.row_stride * EB);
+                             (uint64_t)((int64_t)__builtin_amdgcn_readlane(f.meta.z, first + j) * P.row_stride * EB);
         const uint32_t lim = (uint32_t)(((row + (uint64_t)(P.nvalid * EB - 1)) & ~(uint64_t)3) - start[j]);
 #pragma unroll
         for (int i = 0; i < kRawN<DT>; ++i) {
@@ -459,6 +462,7 @@ __device__ __forceinline__ void unit(const ShParams& P, int64_t tile, int grp, c
   const uint32_t lds = dd::lds_addr(smem);
   const uint32_t spare = lds;
   const uint32_t base = lds + 16 * lane;
+  const int at_form = 4 * (lane < dd::kShFormInts / 4 ? lane : 0);
   // records, loaded ahead of their use: this lane's four ints of the stage's, and this
   // wavefront's offsets (past the last stage the last record is loaded again, and not used)
   const int ints = dd::sh_stage_ints(P.nw);
@@ -477,7 +481,7 @@ __device__ __forceinline__ void unit(const ShParams& P, int64_t tile, int grp, c
   const DD_GLOBAL int32_t* arec = rec + at_add;
   int offs = *arec;
   Stage cur;  // the stage to form
-  cur.meta = *(const DD_GLOBAL i4_t*)(rec + 4 * lane);
+  cur.meta = *(const DD_GLOBAL i4_t*)(rec + at_form);
   asm volatile("" : "+v"(offs), "+v"(cur.meta));
   open_stage<DT>(P, wbase, cur);
   Row<DT> r;
@@ -491,7 +495,7 @@ __device__ __forceinline__ void unit(const ShParams& P, int64_t tile, int grp, c
     if (s >= 0 && s + 1 < nst) arec += ints;
     offs = *arec;
     if (formed + 1 < nst) rec += ints;
-    const i4_t next = *(const DD_GLOBAL i4_t*)(rec + 4 * lane);  // the stage after cur
+    const i4_t next = *(const DD_GLOBAL i4_t*)(rec + at_form);  // the stage after cur
     if (s >= 0) {
       const int flags = __builtin_amdgcn_readlane(now, dd::kShAddInts - 1);  // bundles << 1 | fold
       add_stage(acc, now, base, __builtin_amdgcn_readfirstlane(G * (flags >> 1) - 1));

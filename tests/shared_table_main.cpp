@@ -28,16 +28,18 @@ static int check(const dd_plan* p) {
       int64_t lo = 1 << 30, hi = 0;
       int rows = 0;
       for (int q = 0; q < nb; ++q) {
-        auto head = [&](int i) { return rec[4 * (4 * q + i) + 3]; };
-        const int m = head(0) & 255, np = head(0) >> 8, slot = head(1), base = head(2);
+        auto head = [&](int i) { return rec[4 * (16 * q + i) + 3]; };
+        const int m = head(0), slot = head(1), base = head(2);
         int code[dd::kShMaxPat + 1];
+        int np = 0;
         for (int k = 0; k <= dd::kShMaxPat; ++k) code[k] = rec[4 * (16 * q + k)];
+        while (np < dd::kShMaxPat && code[np] != 64 * dd::kShBlock) ++np;
         if (m < 1 || m > 4 || np < 1 || np > dd::kShMaxPat || slot % 16 || base % 16 || base < dd::kShSpare) return 5;
         if ((int64_t)base + (int64_t)np * slot > p->sh.lds) return 6;
         const int nrow = (slot / 16 + vc - 1) / vc;
-        if (rows + nrow > dd::kShMaxRows) return 7;
-        for (int k = 0; k < nrow; ++k)
-          if (rec[4 * (dd::kShLaneMap + rows++) + 1] != (q | k << 8)) return 7;
+        rows += nrow;
+        const int ends = rec[4 * dd::kShLaneEnds + 3];
+        if (rows > 250 || (q < 3 && ((ends >> (8 * q)) & 255) != rows)) return 7;
         lo = std::min<int64_t>(lo, base), hi = std::max<int64_t>(hi, (int64_t)base + (int64_t)np * slot);
         // raw samples a lane may load past the window start
         const int64_t reach = 4 * ((int64_t)(nrow - 1) * vc + 63) + 8 + (p->dtype == DD_U8 ? dd::kShWords : 0);
@@ -46,7 +48,7 @@ static int check(const dd_plan* p) {
           if (code[k] < 0 || code[k] % dd::kShBlock || code[k] / dd::kShBlock > 63) return 9;
         if (code[np] != 64 * dd::kShBlock) return 9;
         for (int j = 0; j < 4; ++j) {
-          const int off = rec[4 * (4 * q + j) + 1], ch = rec[4 * (4 * q + j) + 2];
+          const int off = rec[4 * (16 * q + j) + 1], ch = rec[4 * (16 * q + j) + 2];
           if (ch < 0 || ch >= p->nchan || off < 0 || off > p->maxdelay) return 10;
           if (j < m && !seen.insert(ch).second) return 11;
         }
@@ -62,8 +64,8 @@ static int check(const dd_plan* p) {
             if (pat >= np || pos + 16 * (3 * 63 + 63) + 16 > slot) return 14;
             for (int j = 0; j < m; ++j) {
               const int shift = j ? (code[pat] / dd::kShBlock >> (2 * (j - 1))) & 3 : 0;
-              const int32_t delay = rec[4 * (4 * q + j) + 1] + shift + pos / 4 + e;
-              if (delay != p->delays[(size_t)rec[4 * (4 * q + j) + 2] * p->ndm + d]) return 15;
+              const int32_t delay = rec[4 * (16 * q + j) + 1] + shift + pos / 4 + e;
+              if (delay != p->delays[(size_t)rec[4 * (16 * q + j) + 2] * p->ndm + d]) return 15;
             }
           }
         }
