@@ -72,6 +72,7 @@ constexpr int sh_max_waves(int dtype) { return dtype == DD_U8 ? 12 : 16; }
 // 16-byte window chunks a wavefront forms per row: lanes past it lack a neighbour's words.
 constexpr int sh_row_chunks(int dtype) { return dtype == DD_U8 ? 62 : 63; }
 constexpr int kShMaxPat = 15;     // patterns of a bundle
+constexpr int kShRecPat = 7;      // patterns of a row's record
 constexpr int kShMaxE = 3;        // largest shift of a channel in a pattern
 // Channels summed in one running FP32 sum before it joins the series' total. Sums of 4 to 128
 // channels, then of the 128-channel blocks, carry the rounding of about 23 adds at full size
@@ -82,24 +83,31 @@ constexpr int kShFold = 128;
 // every explicit tiling, bit for bit.
 constexpr int kShMinChans = 128;
 constexpr int kShMaxBundles = 3;  // bundles of a stage
-constexpr int kShBlock = 132;     // bytes of code per pattern block
+constexpr int kShBlock = 136;     // bytes of code per pattern block
 constexpr int kShSpare = 1024;    // LDS bytes before the stages: where lanes without a chunk write
-// A stage's record, for forming: four ints per lane, 16 lanes per bundle b. x of lane 16 b + i:
-// the code offset of its pattern i (pattern * kShBlock; past the last one 64 * kShBlock); y and
-// z of lane 16 b + j: its channel j's window start and index; w of lanes 16 b, + 1, + 2: its
-// channels, bytes per pattern and LDS offset; w of the lanes below, for the stage: its rows, the
-// rows up to bundles 0, 1 and 2 in bytes, and the samples past a window's start that a row may
-// load. Then per wavefront kShAddInts ints, for adding: its trials' LDS offsets (byte offset of
-// the window's 16-byte boundary | words past it) in bundle order, and in the last int
-// bundles << 1 | fold.
-constexpr int kShFormInts = 4 * 16 * kShMaxBundles;
+// A stage's records: per wavefront one to add from and one to form from.
+// Adding, kShAddInts ints: the LDS offsets of its trials' windows (their 16-byte boundaries) in
+// the stage's bundles, bundle-major; the words their starts lie past those, 2 bits each; the last
+// unit | fold << 8.
+// Forming a row, kShFormInts ints: the window start of the bundle's first channel and the bytes
+// from there to the other three's; the first channel; the LDS offset and the bytes of the first
+// of the record's patterns' sums; row | channels << 8 | 4096 if they run down from the first; 8
+// bytes of pattern numbers, 64 past the last; the samples past the first channel's window start
+// that the row may load; the ints from the group's first record to the wavefront's next row of
+// the stage, or 0. No channels: no row. A group's stages are followed by kShPad of no use, and
+// the first group's preceded by one, so that records can be loaded ahead unchecked.
+constexpr int kShPad = 3;
+constexpr int kShMaxOff = 8192;  // samples between the window starts of a bundle's channels
 constexpr int kShAddInts = 8;
-constexpr int kShLaneRows = 3;
-constexpr int kShLaneEnds = 4;
-constexpr int kShLaneReach = 5;
-constexpr int kShMaxRows = 80;  // rows of a bundle (of a stage: a byte)
-constexpr int sh_stage_ints(int nw) { return kShFormInts + kShAddInts * nw; }
-static_assert(kShG * kShMaxBundles < kShAddInts, "a wavefront's offsets and flags fit its ints");
+constexpr int kShFormInts = 12;
+constexpr int kShRecInts = kShAddInts + kShFormInts;
+constexpr int kShMaxRows = 200;  // rows of a bundle
+// Samples past a window's start that row `row` may load.
+constexpr int sh_reach(int dtype, int row) {
+  return 4 * ((row + 1) * sh_row_chunks(dtype) + 64) + 8 + (dtype == DD_U8 ? kShWords : 0);
+}
+constexpr int sh_stage_ints(int nw) { return kShRecInts * nw; }
+static_assert(kShG * kShMaxBundles <= 6, "a wavefront's units fit its record");
 struct Shared {
   bool on = false;
   int32_t nw = 0;      // wavefronts per workgroup

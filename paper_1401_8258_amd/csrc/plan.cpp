@@ -315,7 +315,9 @@ constexpr int kShMaxTrials = 2 * 16;  // trials of a group
 // One bundle of 1..4 consecutive channels for one group of trials.
 struct Bundle {
   int m, np, slot, rows;  // channels, patterns, bytes of a pattern's sums, rows
-  int32_t off[4], ch[4];
+  int records() const { return rows * ((np + kShRecPat - 1) / kShRecPat); }
+  int32_t off[4], chan;   // window starts; the first channel
+  bool down;              // the channels run down from it
   uint8_t code[kShMaxPat];
   int32_t trial[kShMaxTrials];  // byte offset from the bundle's LDS base | words past 16 bytes
   int64_t bytes() const { return (int64_t)np * slot; }
@@ -329,18 +331,17 @@ constexpr double kShPatClk = 21.0;
 constexpr double kShRowClk = 60.0;
 
 // Channels c0 .. c0 + m - 1 for trials d0 .. d0 + n - 1 (past the last trial: the last one).
-// The reference channel is the bundle's smallest delay, so every relative delay is >= 0.
-// False when the patterns are too many or too wide, or the sums take more than cap bytes.
+// Delays relative to the first channel must not be negative (channels neither rising nor
+// falling in frequency may fail this). False when the patterns are too many or too wide, or the sums take more than cap bytes.
 bool make_bundle(const dd_plan* p, int c0, int m, int d0, int n, int64_t cap, Bundle* b) {
   const int32_t ndm = p->ndm;
   const int nd = std::min(n, (int)ndm - d0);  // trials of the group's own
+  // the channels in order of their delays, up or down from the smallest
   const int32_t* row[4];
-  int ref = 0;
-  for (int j = 0; j < m; ++j) {
-    row[j] = &p->delays[(size_t)(c0 + j) * ndm + d0];
-    if (row[j][nd - 1] < row[ref][nd - 1]) ref = j;
-  }
-  std::swap(row[0], row[ref]);
+  auto last = [&](int j) { return p->delays[(size_t)(c0 + j) * ndm + d0 + nd - 1]; };
+  b->down = m > 1 && last(m - 1) < last(0);
+  b->chan = b->down ? c0 + m - 1 : c0;
+  for (int j = 0; j < m; ++j) row[j] = &p->delays[(size_t)(b->down ? c0 + m - 1 - j : c0 + j) * ndm + d0];
   const int32_t k0 = row[0][0];
   const int64_t chunks = (int64_t)(row[0][nd - 1] - k0) / 4 + 4 * 63 + 1;
   if (16 * chunks > cap) return false;
@@ -350,8 +351,6 @@ bool make_bundle(const dd_plan* p, int c0, int m, int d0, int n, int64_t cap, Bu
   if (b->rows > kShMaxRows) return false;
   int32_t code[kShMaxTrials] = {0};
   b->off[0] = k0;
-  for (int j = 0; j < 4; ++j) b->ch[j] = c0 + (j < m ? j : 0);
-  std::swap(b->ch[0], b->ch[ref]);
   for (int j = 1; j < m; ++j) {
     int32_t rel[kShMaxTrials], lo, hi;
     const int32_t *rj = row[j], *r0 = row[0];
@@ -362,12 +361,12 @@ bool make_bundle(const dd_plan* p, int c0, int m, int d0, int n, int64_t cap, Bu
       lo = r < lo ? r : lo;
       hi = r > hi ? r : hi;
     }
-    if (hi - lo > kShMaxE || lo < 0) return false;
+    if (hi - lo > kShMaxE || lo < 0 || lo > kShMaxOff) return false;
     b->off[j] = k0 + lo;
     for (int t = 0; t < nd; ++t) code[t] |= (rel[t] - lo) << (2 * (j - 1));
   }
-  // channels the bundle lacks repeat its first one (their samples are not used)
-  for (int j = m; j < 4; ++j) b->off[j] = b->off[0], b->ch[j] = b->ch[0];
+  // channels the bundle lacks repeat the first one's start (their samples are not loaded)
+  for (int j = m; j < 4; ++j) b->off[j] = b->off[0];
   int8_t slot_of[64];
   std::memset(slot_of, -1, sizeof(slot_of));
   b->np = 0;
@@ -460,14 +459,22 @@ bool plan_shared(dd_plan* p, int64_t lds_cap) {
   const int nw = maxw / best_div, n = G * nw;
   const int64_t cap = (lds_cap / best_div - kShSpare) / 2 / 256 * 256;
   const int ng = (ndm + n - 1) / n;
-  const int form_ints = kShFormInts, ints = form_ints + kShAddInts * nw;
-  std::vector<int32_t> tab((size_t)(2 * ng + 63) / 64 * 64, 0);
-  int64_t max_stage = 0, max_reach = 0;
+  const int ints = sh_stage_ints(nw);
+  std::vector<int32_t> tab((size_t)(2 * ng + 63) / 64 * 64 + (size_t)ints, 0);
+  int64_t max_reach = 0;
   std::vector<int> order;
-  std::vector<std::pair<size_t, int>> odd;  // records of odd stages and their bundles
+  // a group's records of further rounds, after its stages: (the record to link from, their place)
+  std::vector<int32_t> over;
+  struct Link {
+    bool over;
+    size_t at, to;
+  };
+  std::vector<Link> links;
   for (int g = 0; g < ng; ++g) {
     const size_t first = tab.size();
     int nst = 0;
+    over.clear();
+    links.clear();
     for (int f0 = 0; f0 < nchan; f0 += fold) {
       const int f1 = std::min(nchan, f0 + fold);
       v.clear();
@@ -478,72 +485,92 @@ bool plan_shared(dd_plan* p, int64_t lds_cap) {
       order.resize(v.size());
       for (size_t i = 0; i < v.size(); ++i) order[i] = (int)i;
       std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return v[(size_t)a].np < v[(size_t)b].np; });
-      auto at_rank = [&](size_t i) -> const Bundle& { return v[(size_t)order[i]]; };
       for (size_t i = 0; i < v.size();) {
         // up to kShMaxBundles bundles that fit half the LDS share: as many as leave the fewest
         // wavefronts without a row in the last round of rows
         size_t e = i + 1;
-        int64_t bytes = at_rank(i).bytes();
-        int srows = at_rank(i).rows;
+        int64_t bytes = 0;
+        int nrec = 0;
         double best_fill = 0;
-        for (size_t k = i + 1;; ++k) {
-          const double fill = (double)srows / ((srows + nw - 1) / nw * nw);
-          if (fill >= best_fill) best_fill = fill, e = k;
-          if (k >= v.size() || k - i >= (size_t)kShMaxBundles) break;
-          bytes += at_rank(k).bytes();
-          srows += at_rank(k).rows;
-          if (bytes > cap || srows > 250) break;
+        for (size_t k = i; k < v.size() && k - i < (size_t)kShMaxBundles; ++k) {
+          const Bundle& b = v[(size_t)order[k]];
+          bytes += b.bytes();
+          nrec += b.records();
+          if (bytes > cap) break;
+          const double fill = (double)nrec / ((nrec + nw - 1) / nw * nw);
+          if (fill >= best_fill) best_fill = fill, e = k + 1;
         }
-        const size_t at = tab.size();
-        tab.resize(at + (size_t)ints, 0);
-        int32_t* rec = &tab[at];
-        int64_t base = kShSpare, reach = 0;
-        int32_t rows = 0, ends = 0;
-        for (size_t q = 0; q < e - i; ++q) {
-          const Bundle& b = at_rank(i + q);
-          int32_t* l = rec + 64 * q;  // the bundle's 16 lanes
-          for (int k = 0; k < 16; ++k) l[4 * k] = (k < b.np ? b.code[k] : 64) * kShBlock;
-          for (int j = 0; j < 4; ++j) l[4 * j + 1] = b.off[j], l[4 * j + 2] = b.ch[j];
-          l[3] = b.m;
-          l[7] = b.slot;
-          l[11] = (int32_t)base;
-          rows += b.rows;
-          if (q < 3) ends |= (int32_t)((uint32_t)rows << (8 * q));
-          reach = std::max<int64_t>(reach, 4 * ((int64_t)b.rows * sh_row_chunks(p->dtype) + 64) + 8 +
-                                               (p->dtype == DD_U8 ? kShWords : 0));
-          for (int w = 0; w < nw; ++w)
-            for (int t = 0; t < G; ++t)
-              rec[form_ints + kShAddInts * w + G * (int)q + t] = (int32_t)base + b.trial[G * w + t];
-          base += b.bytes();
+        const int nb = (int)(e - i);
+        const size_t st = tab.size();
+        tab.resize(st + (size_t)ints, 0);
+        int64_t base[kShMaxBundles];  // the bundles' LDS offsets; odd stages use the second half
+        int64_t o = kShSpare + (nst & 1 ? cap : 0);
+        for (int q = 0; q < nb; ++q) base[q] = o, o += v[(size_t)order[i + q]].bytes();
+        for (int w = 0; w < nw; ++w) {
+          int32_t* rec = &tab[st + (size_t)w * kShRecInts];
+          for (int q = 0; q < nb; ++q)
+            for (int t = 0; t < G; ++t) {
+              const int32_t tr = (int32_t)base[q] + v[(size_t)order[i + q]].trial[G * w + t];
+              rec[G * q + t] = tr & ~15;
+              rec[6] |= (tr & 3) << (2 * (G * q + t));
+            }
+          rec[7] = (G * nb - 1) | (e == v.size() ? 256 : 0);
         }
-        for (int q = (int)(e - i); q < 3; ++q) ends |= (int32_t)((uint32_t)0xFF << (8 * q));
-        rec[4 * kShLaneRows + 3] = rows;
-        rec[4 * kShLaneEnds + 3] = ends;
-        rec[4 * kShLaneReach + 3] = (int32_t)reach;
-        for (int w = 0; w < nw; ++w)
-          rec[form_ints + kShAddInts * w + kShAddInts - 1] = (int32_t)(e - i) << 1 | (e == v.size() ? 1 : 0);
-        base -= kShSpare;
-        max_stage = std::max(max_stage, base);
-        max_reach = std::max(max_reach, reach);
-        if (nst & 1) odd.push_back({at, (int)(e - i)});
+        // the rows, those of many patterns in parts and first, round the wavefronts
+        int k = 0;
+        Link last[16];  // each wavefront's last record
+        for (int q = nb - 1; q >= 0; --q) {
+          const Bundle& b = v[(size_t)order[i + q]];
+          const int parts = (b.np + kShRecPat - 1) / kShRecPat;
+          for (int part = 0; part < parts; ++part)
+            for (int row = 0; row < b.rows; ++row, ++k) {
+              const int w = k % nw;
+              size_t at = st + (size_t)w * kShRecInts + kShAddInts;
+              if (k >= nw) {
+                at = over.size();
+                over.resize(at + kShFormInts, 0);
+                links.push_back({last[w].over, last[w].at, at});
+              }
+              last[w] = {k >= nw, at, 0};
+              int32_t* rec = k >= nw ? &over[at] : &tab[at];
+              const int p0 = b.np * part / parts, p1 = b.np * (part + 1) / parts;
+              int32_t far = 0;
+              rec[0] = b.off[0];
+              for (int j = 1; j < 4; ++j) {
+                far = std::max(far, b.off[j] - b.off[0]);
+                rec[j] = (b.off[j] - b.off[0]) * (int32_t)elem_bytes(p->dtype);
+              }
+              rec[4] = b.chan;
+              rec[5] = (int32_t)(base[q] + (int64_t)p0 * b.slot);
+              rec[6] = b.slot;
+              rec[7] = row | b.m << 8 | (b.down ? 4096 : 0);
+              uint8_t code[8];
+              for (int c = 0; c < 8; ++c) code[c] = p0 + c < p1 ? b.code[p0 + c] : 64;
+              std::memcpy(rec + 8, code, 8);
+              rec[10] = far + sh_reach(p->dtype, row);
+              max_reach = std::max<int64_t>(max_reach, rec[10]);
+            }
+        }
+        // wavefronts without a row: no channels and no pattern
+        for (; k < nw; ++k) {
+          int32_t* rec = &tab[st + (size_t)k * kShRecInts + kShAddInts];
+          rec[8] = rec[9] = 0x40404040;
+        }
         ++nst;
         i = e;
       }
     }
+    tab.resize(tab.size() + (size_t)kShPad * ints, 0);
+    const int32_t after = (int32_t)(tab.size() - first);
+    for (const Link& l : links) (l.over ? over[l.at + 11] : tab[l.at + 11]) = after + (int32_t)l.to;
+    tab.insert(tab.end(), over.begin(), over.end());
     tab[2 * (size_t)g] = (int32_t)first;
     tab[2 * (size_t)g + 1] = nst;
     if (tab.size() > ((size_t)1 << 29)) return false;
   }
-  // odd stages use the second half of the LDS
-  for (const auto& o : odd) {
-    int32_t* rec = &tab[o.first];
-    for (int q = 0; q < o.second; ++q) rec[64 * q + 11] += (int32_t)max_stage;
-    for (int w = 0; w < nw; ++w)
-      for (int t = 0; t < G * o.second; ++t) rec[form_ints + kShAddInts * w + t] += (int32_t)max_stage;
-  }
   p->sh.on = true;
   p->sh.nw = nw;
-  p->sh.lds = kShSpare + 2 * max_stage;
+  p->sh.lds = kShSpare + 2 * cap;
   p->sh.mirror = (int32_t)max_reach;
   p->dms_per_group = n;
   p->ngroups = ng;

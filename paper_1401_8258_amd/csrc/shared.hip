@@ -84,40 +84,38 @@ constexpr int kDw = DT == DD_F32 ? 4 : DT == DD_F16 ? 2 : 1;  // dwords of 4 sam
 template <int DT>
 constexpr int kRawN = DT == DD_F32 ? 4 : 2;  // raw dwords a lane holds per channel
 
-// A row of one bundle, wave-uniform, and the raw samples it is formed from.
+// A form record (dd_internal.h) in scalar registers.
+struct Rec {
+  int off, d[3], chan, dst, slot, row, reach, more;
+  uint32_t c0, c1;
+};
+
+__device__ __forceinline__ Rec load_rec(ci32_t p) {
+  Rec k;
+  k.off = p[0];
+#pragma unroll
+  for (int j = 0; j < 3; ++j) k.d[j] = p[1 + j];
+  k.chan = p[4];
+  k.dst = p[5];
+  k.slot = p[6];
+  k.row = p[7];
+  k.c0 = (uint32_t)p[8];
+  k.c1 = (uint32_t)p[9];
+  k.reach = p[10];
+  k.more = p[11];
+  return k;
+}
+
+// What forming a row takes from its record, and the raw samples it is formed from.
 template <int DT>
 struct Row {
-  int live, slot, dst, row, first;      // bytes per pattern, LDS offset, row, its codes' first lane
-  uint32_t sh;                          // per channel 2 bits: bytes its first sample lies past the dword
+  int dst, slot, row;    // LDS offset, bytes per pattern, row
+  uint32_t c0, c1;       // its patterns, a byte each
+  uint32_t sh;           // per channel 2 bits: bytes its first sample lies past the dword
   uint32_t v[4][kRawN<DT>];
 };
 
-// A stage's record (lane l: four ints, dd_internal.h) and its window starts: lane 16 b + j
-// holds channel j's of bundle b.
-struct Stage {
-  i4_t meta;
-  uint64_t start;
-  uint64_t safe;  // lanes whose whole window lies inside the input
-};
-
-__device__ __forceinline__ int lane_w(const Stage& f, int l) { return __builtin_amdgcn_readlane(f.meta.w, l); }
-__device__ __forceinline__ int stage_rows(const Stage& f) { return lane_w(f, dd::kShLaneRows); }
-
-// Window starts: sample wbase + offset of its channel, less ring_len past the ring's end (the
-// difference wraps to a large number before it; ring_len is 0 for linear input).
-template <int DT>
-__device__ __forceinline__ void open_stage(const ShParams& P, uint32_t wbase, Stage& f) {
-  constexpr int EB = kEB<DT>;
-  const uint32_t s0 = wbase + (uint32_t)f.meta.y, s1 = s0 - P.ring;
-  const uint32_t s = s1 < s0 ? s1 : s0;
-  const uint64_t stride = (uint64_t)P.row_stride * EB;
-  const uint64_t at = (uint64_t)(uint32_t)f.meta.z * (uint32_t)stride + (uint64_t)P.in;
-  f.start = at + ((uint64_t)((uint32_t)f.meta.z * (uint32_t)(stride >> 32)) << 32) + (uint64_t)s * EB;
-  const int reach = lane_w(f, dd::kShLaneReach);  // samples past its start a window may load
-  f.safe = __ballot(s + (uint32_t)reach <= P.limit);
-}
-
-// This lane's dwords of one channel, from the scalar window start p and the lane's offset vo.
+// This lane's dwords of one channel, from the scalar channel start p and the lane's offset vo.
 template <int DT>
 __device__ __forceinline__ void load_words(gptr_t p, uint32_t vo, uint32_t (&v)[kRawN<DT>]) {
   if constexpr (DT == DD_F32) {
@@ -132,64 +130,67 @@ __device__ __forceinline__ void load_words(gptr_t p, uint32_t vo, uint32_t (&v)[
   }
 }
 
-// Row t of the stage: its header, and its raw samples' loads: lane l of row r of a bundle loads
-// the 4 window positions 4 (r VC + l) .. + 3 of every channel (8-bit input: also those 1008
-// samples later), in whole dwords; channels the bundle lacks are zeros. Where a window would
-// pass the last sample, each dword is clamped to that of the last sample: positions past it
-// are used by no stored output. The usual case is one block of loads with scalar starts: a
-// choice per channel, or starts in vector registers, made the compiler wait for earlier loads
-// between them (54.2 -> XX ms on the full FP32 workload).
+// The raw samples' loads of a row: lane l of row r of a bundle loads the 4 window positions
+// 4 (r VC + l) .. + 3 of every channel (8-bit input: also those 1008 samples later), in whole
+// dwords; channels the bundle lacks are zeros. The first channel's window starts at sample
+// wbase + its offset, less the ring's length past its end (the difference wraps to a large
+// number before it; the length is 0 for linear input), the others' d bytes further on. Where a
+// window would pass the last sample, each dword is clamped to that of the last sample:
+// positions past it are used by no stored output. The usual case is one block of loads with
+// scalar starts: a choice per channel, or starts in vector registers, made the compiler wait
+// for earlier loads between them. The scalar unit serves all of a CU's wavefronts, one
+// instruction a clock, so the starts are kept to a few operations.
 template <int DT>
-__device__ __forceinline__ void load_row(const ShParams& P, const Stage& f, int t, int lane, Row<DT>& r) {
+__device__ __forceinline__ void load_row(const ShParams& P, const Rec& k, uint32_t wbase, uint32_t lane16, Row<DT>& r) {
   constexpr int VC = dd::sh_row_chunks(DT);
   constexpr int EB = kEB<DT>;
-  r.live = t < stage_rows(f);
-  if (!r.live) return;
-  // the row's bundle, by the rows up to each (bytes; 255 past the last bundle)
-  const int ends = lane_w(f, dd::kShLaneEnds);
-  const int b = (t >= (ends & 255)) + (t >= ((ends >> 8) & 255));
-  static_assert(dd::kShMaxBundles == 3, "two ends tell three bundles apart");
-  const int first = 16 * b;
-  r.row = b ? t - ((ends >> (8 * b - 8)) & 255) : t;
-  r.slot = lane_w(f, first + 1);
-  r.dst = lane_w(f, first + 2);
-  r.first = first;
-  const int m = lane_w(f, first);
-  uint64_t start[4];
+  r.dst = k.dst;
+  r.slot = k.slot;
+  r.c0 = k.c0;
+  r.c1 = k.c1;
+  r.row = k.row & 255;
   r.sh = 0;
+  if (k.row < 256) return;  // no channels
+  // channels run up from `chan`, or down from it
+  const uint64_t stride = (uint64_t)P.row_stride * EB, step = k.row & 4096 ? 0 - stride : stride;
+  const uint32_t s0 = wbase + (uint32_t)k.off, s1 = s0 - P.ring, s = s1 < s0 ? s1 : s0;
+  const bool whole = s + (uint32_t)k.reach <= P.limit;
+  const uint64_t first = (uint64_t)P.in + (uint64_t)(uint32_t)k.chan * stride + (uint64_t)s * EB;
+  const uint32_t vo = (uint32_t)(r.row * VC) * (4 * kDw<DT>) + lane16 / (4 / kDw<DT>);
+  uint64_t base[4];
+  uint32_t at[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)f.start, first + j);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(f.start >> 32), first + j);
-    start[j] = (lo & ~3u) | (uint64_t)hi << 32;
-    if (DT != DD_F32) r.sh |= (lo & 3u) << (2 * j);
-  }
-  uint32_t vo = (uint32_t)(r.row * VC + lane) * (4 * kDw<DT>);
-  const bool whole = ((f.safe >> first) & 15) == 15;
-  if (whole && m == 4) {
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      asm volatile("" : "+v"(vo));  // a 32-bit offset here, so that the load takes the scalar start
-      load_words<DT>((gptr_t)start[j], vo, r.v[j]);
+    base[j] = first + j * step;
+    at[j] = j ? (uint32_t)k.d[j - 1] : 0;
+    if (DT != DD_F32) {
+      at[j] += (uint32_t)base[j] & 3u;
+      base[j] &= ~(uint64_t)3;
+      r.sh |= (at[j] & 3u) << (2 * j);
+      at[j] &= ~3u;
     }
+  }
+  if (whole && (k.row & 1024)) {  // four channels
+#pragma unroll
+    for (int j = 0; j < 4; ++j) load_words<DT>((gptr_t)base[j], vo + at[j], r.v[j]);
   } else {
+    const int m = (k.row >> 8) & 7;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       if (j >= m) {
 #pragma unroll
         for (int i = 0; i < kRawN<DT>; ++i) r.v[j][i] = 0;
       } else if (whole) {
-        asm volatile("" : "+v"(vo));
-        load_words<DT>((gptr_t)start[j], vo, r.v[j]);
+        load_words<DT>((gptr_t)base[j], vo + at[j], r.v[j]);
       } else {
         // a window starts before the last sample of its channel, so lim is not negative
-        const uint64_t row = (uint64_t)P.in +
-                             (uint64_t)((int64_t)__builtin_amdgcn_readlane(f.meta.z, first + j) * P.row_stride * EB);
-        const uint32_t lim = (uint32_t)(((row + (uint64_t)(P.nvalid * EB - 1)) & ~(uint64_t)3) - start[j]);
+        const uint64_t end = (uint64_t)P.in + (uint64_t)(uint32_t)k.chan * stride + (uint64_t)j * step +
+                             (uint64_t)(P.nvalid * EB - 1);
+        const uint32_t lim = (uint32_t)((end & ~(uint64_t)3) - base[j]);
 #pragma unroll
         for (int i = 0; i < kRawN<DT>; ++i) {
-          const uint32_t o = vo + (DT == DD_U8 ? i * dd::kShWords : 4 * i);
-          r.v[j][i] = *(const DD_GLOBAL uint32_t*)((gptr_t)start[j] + (o < lim ? o : lim));
+          const uint32_t o = vo + at[j] + (DT == DD_U8 ? i * dd::kShWords : 4 * i);
+          r.v[j][i] = *(const DD_GLOBAL uint32_t*)((gptr_t)base[j] + (o < lim ? o : lim));
         }
       }
     }
@@ -222,9 +223,9 @@ __device__ __forceinline__ void words(const Row<DT>& r, int j, typename Word<DT>
 // e1, e2, e3: word k of a lane's 4, shifted by e, is its own word k + e, or word k + e - 4 of
 // the next lane (by DPP; the last lane has none, and its sums go to the spare slot). Each of
 // the 64 (e1, e2, e3) is a block of its own, kShBlock bytes of 12 adds (8 bytes each), the LDS
-// write and a jump to the next pattern's block, whose offset lane `first + i` of codes holds;
-// after the last one comes the offset past the table. A jump leaves more than the two
-// instructions a DPP operand has to be older than.
+// write and a jump to the next pattern's block, by its number in the low byte of q; number 64
+// is past the table. A jump leaves more than the two instructions a DPP operand has to be
+// older than.
 #define DD_DPP1 " wave_shl:1 row_mask:0xf bank_mask:0xf bound_ctrl:0\n\t"
 #define DD_FORM_ADD(n, E, U0, U1, U2, U3, W0, W1, W2, W3)                                          \
   ".if " E " == 0\n\t"                                                                            \
@@ -241,13 +242,16 @@ __device__ __forceinline__ void words(const Row<DT>& r, int j, typename Word<DT>
   n "_dpp v114, " W1 ", " U2 DD_DPP1 n "_dpp v115, " W2 ", " U3 DD_DPP1                                \
   ".endif\n\t"
 #define DD_FORM_GO                               \
-  "v_readlane_b32 %[t], %[codes], %[i]\n\t"      \
-  "s_add_u32 %[i], %[i], 1\n\t"                  \
+  "s_and_b32 %[t], s80, 0xff\n\t"                \
+  "s_lshr_b64 s[80:81], s[80:81], 8\n\t"         \
+  "s_mulk_i32 %[t], %c[block]\n\t"               \
   "s_add_u32 vcc_lo, %[tlo], %[t]\n\t"           \
   "s_addc_u32 vcc_hi, %[thi], 0\n\t"             \
   "s_setpc_b64 vcc\n\t"
 #define DD_FORM(n)                                                                                 \
   asm volatile(                                                                                    \
+      "s_mov_b32 s80, %[c0]\n\t"                                                                   \
+      "s_mov_b32 s81, %[c1]\n\t"                                                                   \
       "s_getpc_b64 vcc\n"                                                                          \
       "Ldd_pc_%=:\n\t"                                                                             \
       "s_add_u32 %[tlo], vcc_lo, Ldd_tab_%=-Ldd_pc_%=\n\t"                                         \
@@ -257,9 +261,9 @@ __device__ __forceinline__ void words(const Row<DT>& r, int j, typename Word<DT>
       ".irp e3, 0, 1, 2, 3\n\t"                                                                    \
       ".irp e2, 0, 1, 2, 3\n\t"                                                                    \
       ".irp e1, 0, 1, 2, 3\n\t"                                                                    \
-      DD_FORM_ADD(n, "\\e1", "%5", "%6", "%7", "%8", "%9", "%10", "%11", "%12")                    \
-      DD_FORM_ADD(n, "\\e2", "v112", "v113", "v114", "v115", "%13", "%14", "%15", "%16")           \
-      DD_FORM_ADD(n, "\\e3", "v112", "v113", "v114", "v115", "%17", "%18", "%19", "%20")           \
+      DD_FORM_ADD(n, "\\e1", "%4", "%5", "%6", "%7", "%8", "%9", "%10", "%11")                    \
+      DD_FORM_ADD(n, "\\e2", "v112", "v113", "v114", "v115", "%12", "%13", "%14", "%15")           \
+      DD_FORM_ADD(n, "\\e3", "v112", "v113", "v114", "v115", "%16", "%17", "%18", "%19")           \
       "ds_write_b128 %[dst], v[112:115]\n\t"                                                       \
       "v_add_u32_e32 %[dst], %[step], %[dst]\n\t"                                                  \
       DD_FORM_GO                                                                                   \
@@ -268,17 +272,17 @@ __device__ __forceinline__ void words(const Row<DT>& r, int j, typename Word<DT>
       ".endr\n"                                                                                    \
       "Ldd_end_%=:\n\t"                                                                            \
       ".if Ldd_end_%=-Ldd_tab_%= != 64*%c[block]\n\t.error \"block size\"\n\t.endif"               \
-      : [dst] "+v"(dst), [i] "+s"(i), [t] "=&s"(t), [tlo] "=&s"(tlo), [thi] "=&s"(thi)             \
+      : [dst] "+v"(dst), [t] "=&s"(t), [tlo] "=&s"(tlo), [thi] "=&s"(thi)                          \
       : "v"(w[0][0]), "v"(w[0][1]), "v"(w[0][2]), "v"(w[0][3]), "v"(w[1][0]), "v"(w[1][1]),        \
         "v"(w[1][2]), "v"(w[1][3]), "v"(w[2][0]), "v"(w[2][1]), "v"(w[2][2]), "v"(w[2][3]),        \
-        "v"(w[3][0]), "v"(w[3][1]), "v"(w[3][2]), "v"(w[3][3]), [codes] "v"(codes),                \
+        "v"(w[3][0]), "v"(w[3][1]), "v"(w[3][2]), "v"(w[3][3]), [c0] "s"(c0), [c1] "s"(c1),        \
         [step] "v"(step), [block] "i"(dd::kShBlock)                                                \
-      : "scc", "vcc", "memory", "v112", "v113", "v114", "v115")
-__device__ __forceinline__ void form(const float (&w)[4][4], int codes, int i, uint32_t dst, uint32_t step) {
+      : "scc", "vcc", "memory", "s80", "s81", "v112", "v113", "v114", "v115")
+__device__ __forceinline__ void form(const float (&w)[4][4], uint32_t c0, uint32_t c1, uint32_t dst, uint32_t step) {
   uint32_t t, tlo, thi;
   DD_FORM("v_add_f32");
 }
-__device__ __forceinline__ void form(const uint32_t (&w)[4][4], int codes, int i, uint32_t dst, uint32_t step) {
+__device__ __forceinline__ void form(const uint32_t (&w)[4][4], uint32_t c0, uint32_t c1, uint32_t dst, uint32_t step) {
   uint32_t t, tlo, thi;
   DD_FORM("v_add_u32");
 }
@@ -286,15 +290,15 @@ __device__ __forceinline__ void form(const uint32_t (&w)[4][4], int codes, int i
 // Forms row r: the words of its channels, then the sums.
 // Lanes without a window chunk of their own write to the spare slot.
 template <int DT>
-__device__ __forceinline__ void form_row(const Row<DT>& r, int codes, int lane, uint32_t lds, uint32_t spare) {
+__device__ __forceinline__ void form_row(const Row<DT>& r, uint32_t lane16, uint32_t lds) {
   using T = typename Word<DT>::T;
   constexpr int VC = dd::sh_row_chunks(DT);
   T w[4][4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) words<DT>(r, j, w[j]);
-  const int idx = r.row * VC + lane;
-  const bool mine = lane < VC && idx * 16 < r.slot;
-  form(w, codes, __builtin_amdgcn_readfirstlane(r.first), mine ? lds + r.dst + 16 * idx : spare + 16 * lane, mine ? r.slot : 0);
+  const uint32_t at = (uint32_t)(16 * VC * r.row) + lane16;
+  const bool mine = lane16 < 16 * VC && at < (uint32_t)r.slot;
+  form(w, r.c0, r.c1, lds + (mine ? r.dst + at : lane16), mine ? r.slot : 0);
 }
 
 __device__ __forceinline__ void stage_barrier() {
@@ -313,110 +317,94 @@ __device__ __forceinline__ void stage_barrier() {
 #define DD_SH2(n, A0, A1, A2, A3, W0, W1, W2, W3) DD_OWN(n, A0, W2) DD_OWN(n, A1, W3) DD_NEXT(n, A2, W0) DD_NEXT(n, A3, W1)
 #define DD_SH3(n, A0, A1, A2, A3, W0, W1, W2, W3) DD_OWN(n, A0, W3) DD_NEXT(n, A1, W0) DD_NEXT(n, A2, W1) DD_NEXT(n, A3, W2)
 // Row by row: wait for the row, add it, start the same row of the next unit's window.
-#define DD_WAIT "s_waitcnt lgkmcnt(3)\n\t"
+#define DD_READ0 "ds_read_b128 v[112:115], %[va]\n\t"
+#define DD_READ1 "ds_read_b128 v[116:119], %[va] offset:1008\n\t"
+#define DD_READ2 "ds_read_b128 v[120:123], %[va] offset:2016\n\t"
+#define DD_READ3 "ds_read_b128 v[124:127], %[va] offset:3024\n\t"
+#define DD_WAIT(c) "s_waitcnt lgkmcnt(" #c ")\n\t"
 #define DD_ROWS(SH, n, ...) DD_ROWS_(SH, n, __VA_ARGS__)
-#define DD_ROWS_(SH, n, A0, A1, A2, A3, A4, A5, A6, A7, A8, A9, A10, A11, A12, A13, A14, A15)             \
-  DD_WAIT SH(n, A0, A1, A2, A3, 112, 113, 114, 115) "ds_read_b128 v[112:115], %[va]\n\t"                 \
-  DD_WAIT SH(n, A4, A5, A6, A7, 116, 117, 118, 119) "ds_read_b128 v[116:119], %[va] offset:1008\n\t"     \
-  DD_WAIT SH(n, A8, A9, A10, A11, 120, 121, 122, 123) "ds_read_b128 v[120:123], %[va] offset:2016\n\t"   \
-  DD_WAIT SH(n, A12, A13, A14, A15, 124, 125, 126, 127) "ds_read_b128 v[124:127], %[va] offset:3024\n\t"
-// One unit (a trial's window of one bundle): s0 = its shift, then the next unit's offset in s1.
-// A register that a read in flight will fill is read only after the wait for it.
-#define DD_UNIT(n, K, ...)                      \
-  "s_add_u32 %[i], %[i], 1\n\t"                 \
-  "v_readlane_b32 %[s1], %[meta], %[i]\n\t"     \
-  "s_and_b32 %[s2], %[s1], -16\n\t"             \
-  "v_add_u32 %[va], %[s2], %[base]\n\t"         \
-  "s_cmp_lt_u32 %[s0], 2\n\t"                   \
-  "s_cbranch_scc0 Ldd_c" #K "_%=\n\t"           \
-  "s_cmp_eq_u32 %[s0], 0\n\t"                   \
-  "s_cbranch_scc0 Ldd_b" #K "_%=\n\t"           \
-  DD_ROWS(DD_SH0, n, __VA_ARGS__)               \
-  "s_branch Ldd_e" #K "_%=\n"                   \
-  "Ldd_b" #K "_%=:\n\t"                         \
-  DD_ROWS(DD_SH1, n, __VA_ARGS__)               \
-  "s_branch Ldd_e" #K "_%=\n"                   \
-  "Ldd_c" #K "_%=:\n\t"                         \
-  "s_cmp_eq_u32 %[s0], 2\n\t"                   \
-  "s_cbranch_scc0 Ldd_d" #K "_%=\n\t"           \
-  DD_ROWS(DD_SH2, n, __VA_ARGS__)               \
-  "s_branch Ldd_e" #K "_%=\n"                   \
-  "Ldd_d" #K "_%=:\n\t"                         \
-  DD_ROWS(DD_SH3, n, __VA_ARGS__)               \
-  "Ldd_e" #K "_%=:\n\t"                         \
-  "s_and_b32 %[s0], %[s1], 3\n\t"
+#define DD_ROWS_(SH, n, A0, A1, A2, A3, A4, A5, A6, A7, A8, A9, A10, A11, A12, A13, A14, A15) \
+  DD_WAIT(3) SH(n, A0, A1, A2, A3, 112, 113, 114, 115) DD_READ0                               \
+  DD_WAIT(3) SH(n, A4, A5, A6, A7, 116, 117, 118, 119) DD_READ1                               \
+  DD_WAIT(3) SH(n, A8, A9, A10, A11, 120, 121, 122, 123) DD_READ2                             \
+  DD_WAIT(3) SH(n, A12, A13, A14, A15, 124, 125, 126, 127) DD_READ3
 // The last unit: nothing left to read.
 #define DD_LAST_ROWS(SH, n, ...) DD_LAST_ROWS_(SH, n, __VA_ARGS__)
-#define DD_LAST_ROWS_(SH, n, A0, A1, A2, A3, A4, A5, A6, A7, A8, A9, A10, A11, A12, A13, A14, A15)      \
-  "s_waitcnt lgkmcnt(3)\n\t" SH(n, A0, A1, A2, A3, 112, 113, 114, 115)                                 \
-  "s_waitcnt lgkmcnt(2)\n\t" SH(n, A4, A5, A6, A7, 116, 117, 118, 119)                                 \
-  "s_waitcnt lgkmcnt(1)\n\t" SH(n, A8, A9, A10, A11, 120, 121, 122, 123)                               \
-  "s_waitcnt lgkmcnt(0)\n\t" SH(n, A12, A13, A14, A15, 124, 125, 126, 127)
-#define DD_LAST(n, ...)                         \
-  "Ldd_last_%=:\n\t"                            \
-  "s_cmp_lt_u32 %[s0], 2\n\t"                   \
-  "s_cbranch_scc0 Ldd_lc_%=\n\t"                \
-  "s_cmp_eq_u32 %[s0], 0\n\t"                   \
-  "s_cbranch_scc0 Ldd_lb_%=\n\t"                \
-  DD_LAST_ROWS(DD_SH0, n, __VA_ARGS__)          \
-  "s_branch Ldd_le_%=\n"                        \
-  "Ldd_lb_%=:\n\t"                              \
-  DD_LAST_ROWS(DD_SH1, n, __VA_ARGS__)          \
-  "s_branch Ldd_le_%=\n"                        \
-  "Ldd_lc_%=:\n\t"                              \
-  "s_cmp_eq_u32 %[s0], 2\n\t"                   \
-  "s_cbranch_scc0 Ldd_ld_%=\n\t"                \
-  DD_LAST_ROWS(DD_SH2, n, __VA_ARGS__)          \
-  "s_branch Ldd_le_%=\n"                        \
-  "Ldd_ld_%=:\n\t"                              \
-  DD_LAST_ROWS(DD_SH3, n, __VA_ARGS__)          \
-  "Ldd_le_%=:"
-// A stage's bundles: units (bundle, trial) in order, meta lane `unit` holding the window's
-// LDS byte offset and shift; n is the last unit. All of the window registers' reads end in
-// here: one asm block, so that nothing else touches them while a read is in flight.
-#define DD_STAGE(n)                                 \
-  "s_mov_b32 %[i], 0\n\t"                           \
-  "v_readlane_b32 %[s1], %[meta], 0\n\t"            \
-  "s_and_b32 %[s2], %[s1], -16\n\t"                 \
-  "s_and_b32 %[s0], %[s1], 3\n\t"                   \
-  "v_add_u32 %[va], %[s2], %[base]\n\t"             \
-  "ds_read_b128 v[112:115], %[va]\n\t"              \
-  "ds_read_b128 v[116:119], %[va] offset:1008\n\t"  \
-  "ds_read_b128 v[120:123], %[va] offset:2016\n\t"  \
-  "ds_read_b128 v[124:127], %[va] offset:3024\n"    \
-  "Ldd_l_%=:\n\t"                                   \
-  DD_UNIT(n, 0, DD_U0)                              \
-  "s_cmp_ge_u32 %[i], %[n]\n\t"                     \
-  "s_cbranch_scc1 Ldd_last_%=\n\t"                  \
-  DD_UNIT(n, 1, DD_U1)                              \
-  "s_branch Ldd_l_%=\n"                             \
-  DD_LAST(n, DD_U1)
+#define DD_LAST_ROWS_(SH, n, A0, A1, A2, A3, A4, A5, A6, A7, A8, A9, A10, A11, A12, A13, A14, A15) \
+  DD_WAIT(3) SH(n, A0, A1, A2, A3, 112, 113, 114, 115)                                             \
+  DD_WAIT(2) SH(n, A4, A5, A6, A7, 116, 117, 118, 119)                                             \
+  DD_WAIT(1) SH(n, A8, A9, A10, A11, 120, 121, 122, 123)                                           \
+  DD_WAIT(0) SH(n, A12, A13, A14, A15, 124, 125, 126, 127)
+// The four ways of unit K, whose shift is bits 2 K, 2 K + 1 of %[sh].
+#define DD_WAYS(K, L, ROWS, n, ...)             \
+  "s_bitcmp1_b32 %[sh], 2*" #K "+1\n\t"         \
+  "s_cbranch_scc1 Ldd_" #L #K "c_%=\n\t"        \
+  "s_bitcmp1_b32 %[sh], 2*" #K "\n\t"           \
+  "s_cbranch_scc1 Ldd_" #L #K "b_%=\n\t"        \
+  ROWS(DD_SH0, n, __VA_ARGS__)                  \
+  "s_branch Ldd_" #L #K "e_%=\n"                \
+  "Ldd_" #L #K "b_%=:\n\t"                      \
+  ROWS(DD_SH1, n, __VA_ARGS__)                  \
+  "s_branch Ldd_" #L #K "e_%=\n"                \
+  "Ldd_" #L #K "c_%=:\n\t"                      \
+  "s_bitcmp1_b32 %[sh], 2*" #K "\n\t"           \
+  "s_cbranch_scc1 Ldd_" #L #K "d_%=\n\t"        \
+  ROWS(DD_SH2, n, __VA_ARGS__)                  \
+  "s_branch Ldd_" #L #K "e_%=\n"                \
+  "Ldd_" #L #K "d_%=:\n\t"                      \
+  ROWS(DD_SH3, n, __VA_ARGS__)                  \
+  "Ldd_" #L #K "e_%=:\n\t"
+#define DD_U0 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15
+#define DD_U1 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31
+// Unit K reads ahead the window at %[aN] (unit K + 1's); a bundle's second unit is the last one
+// if %[end] says so.
+#define DD_UNIT(K, N, n, ...) "v_add_u32 %[va], %[a" #N "], %[base]\n\t" DD_WAYS(K, u, DD_ROWS, n, __VA_ARGS__)
+#define DD_END(K, n)                            \
+  "s_cmp_eq_u32 %[end], " #K "\n\t"               \
+  "s_cbranch_scc0 Ldd_go" #K "_%=\n\t"          \
+  DD_WAYS(K, l, DD_LAST_ROWS, n, DD_U1)         \
+  "s_branch Ldd_out_%=\n"                       \
+  "Ldd_go" #K "_%=:\n\t"
+// A stage's bundles: units (bundle, trial) in order, unit K's window at LDS offset %[aK] and
+// its shift in %[sh]; %[end] is the last unit. All of the window registers' reads end in here:
+// one asm block, so that nothing else touches them while a read is in flight.
+#define DD_STAGE(n)                                                                                       \
+  asm volatile("v_add_u32 %[va], %[a0], %[base]\n\t" DD_READ0 DD_READ1 DD_READ2 DD_READ3                  \
+               DD_UNIT(0, 1, n, DD_U0) DD_END(1, n) DD_UNIT(1, 2, n, DD_U1)                               \
+               DD_UNIT(2, 3, n, DD_U0) DD_END(3, n) DD_UNIT(3, 4, n, DD_U1)                               \
+               DD_UNIT(4, 5, n, DD_U0) DD_WAYS(5, l, DD_LAST_ROWS, n, DD_U1)                              \
+               "Ldd_out_%=:"                                                                              \
+               : DD_ACC(0), DD_ACC(1), [va] "=&v"(va)                                                     \
+               : [base] "v"(base), [end] "s"(k.last & 255), [sh] "s"(k.sh), [a0] "s"(k.a[0]), [a1] "s"(k.a[1]),   \
+                 [a2] "s"(k.a[2]), [a3] "s"(k.a[3]), [a4] "s"(k.a[4]), [a5] "s"(k.a[5])                   \
+               : "scc", "memory", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", \
+                 "v121", "v122", "v123", "v124", "v125", "v126", "v127")
 #define DD_ACC(g)                                                                                          \
   "+v"(acc[g][0]), "+v"(acc[g][1]), "+v"(acc[g][2]), "+v"(acc[g][3]), "+v"(acc[g][4]), "+v"(acc[g][5]),    \
       "+v"(acc[g][6]), "+v"(acc[g][7]), "+v"(acc[g][8]), "+v"(acc[g][9]), "+v"(acc[g][10]),                \
       "+v"(acc[g][11]), "+v"(acc[g][12]), "+v"(acc[g][13]), "+v"(acc[g][14]), "+v"(acc[g][15])
-#define DD_STAGE_TMP [va] "=&v"(va), [i] "=&s"(i), [s0] "=&s"(s0), [s1] "=&s"(s1), [s2] "=&s"(s2)
-#define DD_STAGE_USE [meta] "v"(meta), [base] "v"(base), [n] "s"(n)
-#define DD_STAGE_CLOBBER                                                                                  \
-  "scc", "memory", "v112", "v113", "v114", "v115", "v116", "v117", "v118", "v119", "v120", "v121", "v122", \
-      "v123", "v124", "v125", "v126", "v127"
 
-#define DD_U0 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15
-#define DD_U1 16, 17, 18, 19, 20, 21, 22, 23, 24, 25, 26, 27, 28, 29, 30, 31
-static_assert(dd::kShG == 2, "the stage's code walks two trials");
-__device__ __forceinline__ void add_stage(float (&acc)[2][16], int meta, uint32_t base, int n) {
-  uint32_t va, i, s0, s1, s2;
-  asm volatile(DD_STAGE("v_add_f32")
-               : DD_ACC(0), DD_ACC(1), DD_STAGE_TMP
-               : DD_STAGE_USE
-               : DD_STAGE_CLOBBER);
+// An add record (dd_internal.h) in scalar registers.
+struct Adds {
+  int a[6], sh, last;  // last: the last unit | fold << 8
+};
+__device__ __forceinline__ Adds load_adds(ci32_t p) {
+  Adds k;
+#pragma unroll
+  for (int i = 0; i < 6; ++i) k.a[i] = p[i];
+  k.sh = p[6];
+  k.last = p[7];
+  return k;
 }
-__device__ __forceinline__ void add_stage(uint32_t (&acc)[2][16], int meta, uint32_t base, int n) {
-  uint32_t va, i, s0, s1, s2;
-  asm volatile(DD_STAGE("v_add_u32")
-               : DD_ACC(0), DD_ACC(1), DD_STAGE_TMP
-               : DD_STAGE_USE
-               : DD_STAGE_CLOBBER);
+
+static_assert(dd::kShG == 2 && dd::kShMaxBundles == 3, "a stage's code walks two trials of up to three bundles");
+__device__ __forceinline__ void add_stage(float (&acc)[2][16], const Adds& k, uint32_t base) {
+  uint32_t va;
+  DD_STAGE("v_add_f32");
+}
+__device__ __forceinline__ void add_stage(uint32_t (&acc)[2][16], const Adds& k, uint32_t base) {
+  uint32_t va;
+  DD_STAGE("v_add_u32");
 }
 
 // Blocks of kShFold channels (FP32) or 256 channels (8-bit codes: 255 x 256 < 2^16) close into
@@ -460,75 +448,74 @@ __device__ __forceinline__ void unit(const ShParams& P, int64_t tile, int grp, c
   const int nst = tab[2 * grp + 1];
   const uint32_t wbase = (uint32_t)(P.ring ? (P.win0 + t0) % P.ring : t0);
   const uint32_t lds = dd::lds_addr(smem);
-  const uint32_t spare = lds;
-  const uint32_t base = lds + 16 * lane;
-  const int at_form = 4 * (lane < dd::kShFormInts / 4 ? lane : 0);
-  // records, loaded ahead of their use: this lane's four ints of the stage's, and this
-  // wavefront's offsets (past the last stage the last record is loaded again, and not used)
-  const int ints = dd::sh_stage_ints(P.nw);
-  const DD_GLOBAL int32_t* rec = (const DD_GLOBAL int32_t*)P.tab + tab[2 * grp];
-  const int at_add = dd::kShFormInts + dd::kShAddInts * wv + (lane & (dd::kShAddInts - 1));
-
+  const uint32_t lane16 = 16 * lane;  // the spare slot comes first in the LDS
   // Every wavefront alternates adding a stage with forming the next one. Between two barriers
   // the two are independent; half of a SIMD's wavefronts form first (their barrier comes
   // between the adds and the forming, one stage further on), so that the LDS reads of some run
   // beside the LDS writes of others. The first row of a stage's raw samples is loaded when the
-  // stage before has been formed.
-  const bool form_first = (wv >> 2) & 1;
-  // Loads return in order, so what an iteration needs beside the raw samples (the next record
-  // to form from, the next offsets) is loaded at its start and waited on before the next raw
-  // loads go out.
-  const DD_GLOBAL int32_t* arec = rec + at_add;
-  int offs = *arec;
-  Stage cur;  // the stage to form
-  cur.meta = *(const DD_GLOBAL i4_t*)(rec + at_form);
-  asm volatile("" : "+v"(offs), "+v"(cur.meta));
-  open_stage<DT>(P, wbase, cur);
-  Row<DT> r;
-  load_row<DT>(P, cur, wv, lane, r);
-  int formed = 0;
-  int s = form_first ? -2 : -1;
+  // stage before has been formed. Records before the first stage and past the last one are
+  // readable and go unused.
+  const int ints = dd::sh_stage_ints(P.nw);
+  ci32_t group = tab + tab[2 * grp];
+  const int form_first = (wv >> 2) & 1;
+  int s = -1 - form_first;
   asm volatile("" : "+s"(s));  // one copy of the loop body: no peeled first iteration
+  Row<DT> r;
+  int more;
+  {
+    const Rec k = load_rec(group + dd::kShRecInts * wv + dd::kShAddInts);
+    load_row<DT>(P, k, wbase, lane16, r);
+    more = k.more;
+  }
+  ci32_t rec = group + dd::kShRecInts * wv + (s + 1) * ints;  // stage s + 1's record
+  const int form_at = (1 + form_first) * ints + dd::kShAddInts;  // from there to the form record after next
+  Adds adds = load_adds(rec);  // waited on here, not in the loop
+  asm volatile("" : "+s"(adds.a[0]), "+s"(adds.a[1]), "+s"(adds.a[2]), "+s"(adds.a[3]), "+s"(adds.a[4]),
+               "+s"(adds.a[5]), "+s"(adds.sh), "+s"(adds.last));
 #pragma nounroll
   for (; s < nst; ++s) {
-    const int now = offs;
-    if (s >= 0 && s + 1 < nst) arec += ints;
-    offs = *arec;
-    if (formed + 1 < nst) rec += ints;
-    const i4_t next = *(const DD_GLOBAL i4_t*)(rec + at_form);  // the stage after cur
     if (s >= 0) {
-      const int flags = __builtin_amdgcn_readlane(now, dd::kShAddInts - 1);  // bundles << 1 | fold
-      add_stage(acc, now, base, __builtin_amdgcn_readfirstlane(G * (flags >> 1) - 1));
-      if (flags & 1) {
+      add_stage(acc, adds, lds + lane16);
+      if (adds.last >> 8) {
 #pragma unroll
         for (int g = 0; g < G; ++g) fold(tot[g], acc[g]);
       }
     }
     if (form_first && s >= -1) stage_barrier();
-    if (formed < nst) {
-      const int rows = stage_rows(cur);
-      if (r.live) form_row<DT>(r, cur.meta.x, lane, lds, spare);
-      for (int t = wv + P.nw; t < rows; t += P.nw) {
-        load_row<DT>(P, cur, t, lane, r);
-        form_row<DT>(r, cur.meta.x, lane, lds, spare);
+    // the next records: after the adds, whose waits for LDS reads would take these loads in, and
+    // back by the time the rows have been formed
+    const Adds ahead = load_adds(rec);
+    const Rec k = load_rec(rec + form_at);
+    rec += ints;
+    if (s + 1 + form_first < nst) {
+      // this wavefront's rows of the stage (one, or more by links), then the next stage's first
+      for (;;) {
+        form_row<DT>(r, lane16, lds);
+        Rec x = k;
+        const bool link = more != 0;
+        if (link) x = load_rec(group + more);
+        load_row<DT>(P, x, wbase, lane16, r);
+        more = x.more;
+        if (!link) break;
       }
-      ++formed;
     }
-    cur.meta = next;
-    asm volatile("" : "+v"(offs), "+v"(cur.meta));
-    if (formed < nst) {
-      open_stage<DT>(P, wbase, cur);
-      load_row<DT>(P, cur, wv, lane, r);
-    }
+    adds = ahead;
     if (!form_first) stage_barrier();
   }
 
-  // outputs, and FP64 sums of the tile's outputs per trial (a fixed tree)
+  // outputs, and FP64 sums of the tile's outputs per trial (a fixed tree). The parameters are
+  // read again here, so that they take no registers in the loop.
+  const __attribute__((address_space(4))) ShParams* Q =
+      (const __attribute__((address_space(4))) ShParams*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(Q));
+  float* const out = Q->out;
+  double* const part = Q->part;
+  const int64_t nout = Q->nout;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
-    const int d = grp * P.per_group + wv * G + g;
-    if (d >= P.ndm) break;
-    float* row = P.out + (int64_t)d * P.out_stride;
+    const int d = grp * Q->per_group + wv * G + g;
+    if (d >= Q->ndm) break;
+    float* row = out + (int64_t)d * Q->out_stride;
     const bool vec = ((uint64_t)row & 15) == 0;
     double s1 = 0.0, s2 = 0.0;
 #pragma unroll
@@ -540,27 +527,27 @@ __device__ __forceinline__ void unit(const ShParams& P, int64_t tile, int grp, c
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = as_out(tot[g][16 * h + 4 * i + e]);
         if (lane < kRow) {
-          if (t + 4 <= P.nout && vec) {
+          if (t + 4 <= nout && vec) {
             *reinterpret_cast<float4*>(row + t) = make_float4(v[0], v[1], v[2], v[3]);
           } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-              if (t + e < P.nout) row[t + e] = v[e];
+              if (t + e < nout) row[t + e] = v[e];
           }
 #pragma unroll
           for (int e = 0; e < 4; ++e)
-            if (t + e < P.nout) {
+            if (t + e < nout) {
               const double x = (double)v[e];
               s1 += x;
               s2 += x * x;
             }
         }
       }
-    if (P.part) {
+    if (part) {
       s1 = dd::wave_sum_lane0(s1);
       s2 = dd::wave_sum_lane0(s2);
       if (lane == 0) {
-        double* q = P.part + ((int64_t)d * P.ntile + tile) * 2;
+        double* q = part + ((int64_t)d * Q->ntile + tile) * 2;
         q[0] = s1;
         q[1] = s2;
       }

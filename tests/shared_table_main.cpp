@@ -2,11 +2,17 @@
 // must be the delay table's, and every LDS and input position must lie inside its buffer.
 #include <cmath>
 #include <cstdio>
+#include <map>
 #include <random>
 #include <set>
 #include <vector>
 
 #include "../paper_1401_8258_amd/csrc/dd_internal.h"
+
+struct Form {  // one bundle's patterns of a stage, by LDS offset
+  int m, slot, chan[4], off[4], shift[4];
+  std::set<int> rows;
+};
 
 static int check(const dd_plan* p) {
   const std::vector<int32_t>& t = p->dev_table;
@@ -16,68 +22,85 @@ static int check(const dd_plan* p) {
   if (p->sh.lds > dd::kLdsBytes || p->dms_per_group != n || p->ngroups != (p->ndm + n - 1) / n) return 2;
   for (int g = 0; g < p->ngroups; ++g) {
     const int64_t at = t[2 * (size_t)g], nst = t[2 * (size_t)g + 1];
-    if (at < 2 * p->ngroups || nst < 1 || at + nst * ints > (int64_t)t.size()) return 3;
+    const int64_t end = g + 1 < p->ngroups ? t[2 * (size_t)g + 2] : (int64_t)t.size();
+    if (at < 2 * p->ngroups || nst < 1 || at - ints < 2 * p->ngroups || at + (nst + dd::kShPad) * ints > end || end > (int64_t)t.size()) return 3;
     std::set<int> seen;
     int64_t prev_lo = -1, prev_hi = -1;
     int open = 0;  // channels since the last fold
     for (int64_t s = 0; s < nst; ++s) {
-      const int32_t* rec = &t[(size_t)(at + s * ints)];
-      const int32_t* add = rec + dd::kShFormInts;
-      const int nb = add[dd::kShAddInts - 1] >> 1, fold = add[dd::kShAddInts - 1] & 1;
-      if (nb < 1 || nb > dd::kShMaxBundles || nb * G >= dd::kShAddInts) return 4;
+      const int32_t* st = &t[(size_t)(at + s * ints)];
+      std::map<int, Form> forms;  // by LDS offset
       int64_t lo = 1 << 30, hi = 0;
-      int rows = 0;
-      for (int q = 0; q < nb; ++q) {
-        auto head = [&](int i) { return rec[4 * (16 * q + i) + 3]; };
-        const int m = head(0), slot = head(1), base = head(2);
-        int code[dd::kShMaxPat + 1];
-        int np = 0;
-        for (int k = 0; k <= dd::kShMaxPat; ++k) code[k] = rec[4 * (16 * q + k)];
-        while (np < dd::kShMaxPat && code[np] != 64 * dd::kShBlock) ++np;
-        if (m < 1 || m > 4 || np < 1 || np > dd::kShMaxPat || slot % 16 || base % 16 || base < dd::kShSpare) return 5;
-        if ((int64_t)base + (int64_t)np * slot > p->sh.lds) return 6;
-        const int nrow = (slot / 16 + vc - 1) / vc;
-        rows += nrow;
-        const int ends = rec[4 * dd::kShLaneEnds + 3];
-        if (rows > 250 || (q < 3 && ((ends >> (8 * q)) & 255) != rows)) return 7;
-        lo = std::min<int64_t>(lo, base), hi = std::max<int64_t>(hi, (int64_t)base + (int64_t)np * slot);
-        // raw samples a lane may load past the window start
-        const int64_t reach = 4 * ((int64_t)(nrow - 1) * vc + 63) + 8 + (p->dtype == DD_U8 ? dd::kShWords : 0);
-        if (reach > rec[4 * dd::kShLaneReach + 3] || reach > dd::ring_mirror(p)) return 8;
-        for (int k = 0; k < np; ++k)
-          if (code[k] < 0 || code[k] % dd::kShBlock || code[k] / dd::kShBlock > 63) return 9;
-        if (code[np] != 64 * dd::kShBlock) return 9;
-        for (int j = 0; j < 4; ++j) {
-          const int off = rec[4 * (16 * q + j) + 1], ch = rec[4 * (16 * q + j) + 2];
-          if (ch < 0 || ch >= p->nchan || off < 0 || off > p->maxdelay) return 10;
-          if (j < m && !seen.insert(ch).second) return 11;
-        }
-        open += m;
-        for (int w = 0; w < nw; ++w) {
-          if (add[dd::kShAddInts * w + dd::kShAddInts - 1] != (nb << 1 | fold)) return 12;
-          for (int k = 0; k < G; ++k) {
-            const int d = std::min(g * n + w * G + k, p->ndm - 1);
-            const int32_t o = add[dd::kShAddInts * w + G * q + k];
-            const int32_t rel = (o & ~15) - base, e = o & 3;
-            if ((o & 12) || rel < 0) return 13;
-            const int pat = rel / slot, pos = rel % slot;
-            if (pat >= np || pos + 16 * (3 * 63 + 63) + 16 > slot) return 14;
+      for (int w = 0; w < nw; ++w) {
+        const int32_t* rec = st + w * dd::kShRecInts + dd::kShAddInts;
+        for (int rounds = 0;; ++rounds) {
+          if (rounds > 1000) return 4;
+          const int m = (rec[7] >> 8) & 7, row = rec[7] & 255, step = rec[7] & 4096 ? -1 : 1;
+          const uint8_t* code = reinterpret_cast<const uint8_t*>(rec + 8);
+          if (m > 4) return 5;
+          if (m == 0 && (code[0] != 64 || rec[11] || rounds)) return 6;
+          if (m && code[0] == 64) return 6;
+          for (int k = 0; m && code[k] != 64; ++k) {
+            if (k >= dd::kShRecPat || code[k] > 63) return 7;
+            const int dst = rec[5] + k * rec[6];
+            Form f{m, rec[6], {}, {}, {}, {}};
             for (int j = 0; j < m; ++j) {
-              const int shift = j ? (code[pat] / dd::kShBlock >> (2 * (j - 1))) & 3 : 0;
-              const int32_t delay = rec[4 * (16 * q + j) + 1] + shift + pos / 4 + e;
-              if (delay != p->delays[(size_t)rec[4 * (16 * q + j) + 2] * p->ndm + d]) return 15;
+              f.chan[j] = rec[4] + j * step;
+              f.off[j] = rec[0] + (j ? rec[j] / (int)dd::elem_bytes(p->dtype) : 0);
+              if (f.off[j] - rec[0] + dd::sh_reach(p->dtype, row) > rec[10]) return 8;
+              f.shift[j] = j ? (code[k] >> (2 * (j - 1))) & 3 : 0;
+              if (f.chan[j] < 0 || f.chan[j] >= p->nchan || f.off[j] < 0 || f.off[j] > p->maxdelay) return 8;
             }
+            if (rec[6] % 16 || rec[5] % 16 || rec[5] < dd::kShSpare || dst + rec[6] > p->sh.lds) return 9;
+            auto it = forms.insert({dst, f}).first;
+            if (it->second.chan[0] != f.chan[0] || it->second.m != m || it->second.slot != f.slot) return 10;
+            if (!it->second.rows.insert(row).second) return 11;
+            lo = std::min<int64_t>(lo, dst), hi = std::max<int64_t>(hi, (int64_t)dst + rec[6]);
           }
+          // raw samples a lane may load past the window start
+          const int64_t reach = 4 * ((int64_t)row * vc + 63) + 8 + (p->dtype == DD_U8 ? dd::kShWords : 0);
+          if (m && (reach > dd::sh_reach(p->dtype, row) || rec[10] > dd::ring_mirror(p))) return 12;
+          if (!rec[11]) break;
+          if (rec[11] < nst * ints || at + rec[11] + dd::kShFormInts > end) return 13;
+          rec = &t[(size_t)(at + rec[11])];
         }
       }
-      if (rows != rec[4 * dd::kShLaneRows + 3]) return 16;
-      if (s > 0 && lo < prev_hi && prev_lo < hi) return 17;  // written while the stage before is read
+      int64_t past = 0;  // the sums of a stage do not overlap and their rows cover their windows
+      for (const auto& kv : forms) {
+        if (kv.first < past) return 14;
+        past = (int64_t)kv.first + kv.second.slot;
+        if ((int)kv.second.rows.size() != (kv.second.slot / 16 + vc - 1) / vc) return 15;
+        if (*kv.second.rows.rbegin() + 1 != (int)kv.second.rows.size()) return 15;
+      }
+      const int units = (st[7] & 255) + 1, fold = st[7] >> 8;
+      if (units % G || units > G * dd::kShMaxBundles) return 16;
+      for (int w = 0; w < nw; ++w) {
+        const int32_t* add = st + w * dd::kShRecInts;
+        if (add[7] != st[7]) return 17;
+        for (int u = 0; u < units; ++u) {
+          const int d = std::min(g * n + w * G + u % G, p->ndm - 1);
+          auto it = forms.upper_bound(add[u]);
+          if (add[u] & 15 || it == forms.begin()) return 18;
+          --it;
+          const Form& f = it->second;
+          const int pos = add[u] - it->first;
+          if (pos + 16 * (3 * 63 + 63) + 16 > f.slot) return 19;
+          for (int j = 0; j < f.m; ++j) {
+            const int32_t delay = f.off[j] + f.shift[j] + pos / 4 + ((add[6] >> (2 * u)) & 3);
+            if (delay != p->delays[(size_t)f.chan[j] * p->ndm + d]) return 20;
+            // every trial takes every channel of the stage once
+            if (w == 0 && u % G == 0 && !seen.insert(f.chan[j]).second) return 21;
+          }
+          if (w == 0 && u % G == 0) open += f.m;
+        }
+      }
+      if (s > 0 && lo < prev_hi && prev_lo < hi) return 22;  // written while the stage before is read
       prev_lo = lo, prev_hi = hi;
-      if (open > (p->dtype == DD_U8 ? 256 : dd::kShFold)) return 18;
+      if (open > (p->dtype == DD_U8 ? 256 : dd::kShFold)) return 23;
       if (fold) open = 0;
-      else if (s + 1 == nst) return 19;  // the last stage folds
+      else if (s + 1 == nst) return 24;  // the last stage folds
     }
-    if ((int)seen.size() != p->nchan) return 20;
+    if ((int)seen.size() != p->nchan) return 25;
   }
   return 0;
 }
