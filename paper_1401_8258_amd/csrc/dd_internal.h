@@ -65,10 +65,10 @@ inline int64_t align_up(int64_t x, int64_t a = kAlign) { return (x + a - 1) / a 
 
 // Shared-sum form (csrc/shared.hip): words of a time tile (4 rows x 63 lanes x 4).
 constexpr int kShWords = 1008;
-// Trials per wavefront, and wavefronts that a CU holds: FP32 and FP16 sums fit 128 registers
-// (16 wavefronts); 8-bit input keeps two totals per word and takes 168 (12 wavefronts).
+// Trials per wavefront and wavefronts of a CU: the sums of two trials (8-bit input: two totals
+// per word) fit 128 registers beside a window, so 16 wavefronts.
 constexpr int kShG = 2;
-constexpr int sh_max_waves(int dtype) { return dtype == DD_U8 ? 12 : 16; }
+constexpr int kShWaves = 16;
 // 16-byte window chunks a wavefront forms per row: lanes past it lack a neighbour's words.
 constexpr int sh_row_chunks(int dtype) { return dtype == DD_U8 ? 62 : 63; }
 constexpr int kShMaxPat = 15;     // patterns of a bundle

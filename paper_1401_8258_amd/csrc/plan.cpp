@@ -428,7 +428,7 @@ bool bundle_quad(const dd_plan* p, int c0, int c1, int d0, int n, int64_t cap, s
 bool plan_shared(dd_plan* p, int64_t lds_cap) {
   const int32_t nchan = p->nchan, ndm = p->ndm;
   const int fold = p->dtype == DD_U8 ? 256 : kShFold;
-  const int maxw = sh_max_waves(p->dtype), G = kShG;
+  const int maxw = kShWaves, G = kShG;
   // Wavefronts per workgroup: one, two or four workgroups share a CU's wavefront slots and its
   // LDS. More trials per workgroup share each sum, fewer keep windows short where delays
   // grow by many samples per trial. The cheapest in LDS clocks per trial on a sample of the

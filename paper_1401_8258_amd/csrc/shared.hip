@@ -442,13 +442,12 @@ __device__ __forceinline__ void unit(const ShParams& P, int64_t tile, int grp, c
 #pragma unroll
     for (int i = 0; i < 16 * H; ++i) tot[g][i] = T(0);
   }
-  const int lane = threadIdx.x & 63;
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   ci32_t tab = (ci32_t)P.tab;
   const int nst = tab[2 * grp + 1];
   const uint32_t wbase = (uint32_t)(P.ring ? (P.win0 + t0) % P.ring : t0);
   const uint32_t lds = dd::lds_addr(smem);
-  const uint32_t lane16 = 16 * lane;  // the spare slot comes first in the LDS
+  const uint32_t lane16 = 16 * (threadIdx.x & 63);  // the spare slot comes first in the LDS
   // Every wavefront alternates adding a stage with forming the next one. Between two barriers
   // the two are independent; half of a SIMD's wavefronts form first (their barrier comes
   // between the adds and the forming, one stage further on), so that the LDS reads of some run
@@ -488,16 +487,16 @@ __device__ __forceinline__ void unit(const ShParams& P, int64_t tile, int grp, c
     const Rec k = load_rec(rec + form_at);
     rec += ints;
     if (s + 1 + form_first < nst) {
-      // this wavefront's rows of the stage (one, or more by links), then the next stage's first
-      for (;;) {
-        form_row<DT>(r, lane16, lds);
-        Rec x = k;
-        const bool link = more != 0;
-        if (link) x = load_rec(group + more);
+      // this wavefront's row of the stage, further ones by links, then the next stage's first
+      form_row<DT>(r, lane16, lds);
+      while (more) {
+        const Rec x = load_rec(group + more);
         load_row<DT>(P, x, wbase, lane16, r);
         more = x.more;
-        if (!link) break;
+        form_row<DT>(r, lane16, lds);
       }
+      load_row<DT>(P, k, wbase, lane16, r);
+      more = k.more;
     }
     adds = ahead;
     if (!form_first) stage_barrier();
@@ -508,6 +507,9 @@ __device__ __forceinline__ void unit(const ShParams& P, int64_t tile, int grp, c
   const __attribute__((address_space(4))) ShParams* Q =
       (const __attribute__((address_space(4))) ShParams*)__builtin_amdgcn_kernarg_segment_ptr();
   asm volatile("" : "+s"(Q));
+  uint32_t l16 = lane16;
+  asm volatile("" : "+v"(l16));
+  const int lane = (int)(l16 >> 4);
   float* const out = Q->out;
   double* const part = Q->part;
   const int64_t nout = Q->nout;
@@ -558,7 +560,7 @@ __device__ __forceinline__ void unit(const ShParams& P, int64_t tile, int grp, c
 // One unit per workgroup; XCD x (workgroups x, x + 8, ...) takes a contiguous run of units,
 // tile-major, so the DM groups of a tile share that XCD's L2.
 template <int DT>
-__global__ __launch_bounds__(64 * dd::sh_max_waves(DT)) void dedisp_shared(ShParams P) {
+__global__ __launch_bounds__(64 * dd::kShWaves) void dedisp_shared(ShParams P) {
   extern __shared__ __align__(16) char smem[];
   const int64_t lin = blockIdx.x;
   const int64_t per = (P.nitems + 7) / 8;

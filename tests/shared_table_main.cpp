@@ -18,7 +18,7 @@ static int check(const dd_plan* p) {
   const std::vector<int32_t>& t = p->dev_table;
   const int nw = p->sh.nw, G = dd::kShG, n = G * nw;
   const int ints = dd::sh_stage_ints(nw), vc = dd::sh_row_chunks(p->dtype);
-  if (nw < 1 || nw > dd::sh_max_waves(p->dtype)) return 1;
+  if (nw < 1 || nw > dd::kShWaves) return 1;
   if (p->sh.lds > dd::kLdsBytes || p->dms_per_group != n || p->ngroups != (p->ndm + n - 1) / n) return 2;
   for (int g = 0; g < p->ngroups; ++g) {
     const int64_t at = t[2 * (size_t)g], nst = t[2 * (size_t)g + 1];
