@@ -34,3 +34,25 @@ def test_detrend_rows_at_any_offset(torch, n):
     assert np.max(np.abs(got[:, :n] - want)) <= 1e-6
     np.testing.assert_allclose(rms.cpu().numpy(), want_rms, rtol=1e-6, atol=1e-6)
     assert np.all(got[:, n:] == -7.0)
+
+
+@pytest.mark.parametrize("nchan,n", [(31, 63), (32, 64), (33, 65), (64, 127), (95, 1)])
+def test_spectrum_clip_split(torch, nchan, n):
+    import paper_1401_8258_amd as dd
+    print(f"case: spectrum clip {nchan}x{n}", flush=True)
+    rng = np.random.default_rng(nchan)
+    x = (10.0 + rng.standard_normal((nchan, n + 1))).astype(np.float32)
+    hit = (np.arange(n) % 5 == 0) & (n > 1)
+    x[:, :n][:, hit] += 4.0
+    dev = torch.from_numpy(x).cuda()
+    fit, _, mean, _ = dd.rfi_mitigate(dev[:, :n], 1, 0.0, 0, 2.0)  # the spectrum stage and the correction
+    dist = np.abs(x[:, :n].astype(np.float64).mean(axis=0) - mean)
+    assert np.min(np.abs(dist - 2.0)) > 1e-3  # no decision near the threshold
+    np.testing.assert_array_equal(dist > 2.0, hit)
+    want = x[:, :n].astype(np.float64) - fit.astype(np.float32)[:, None]
+    want[:, hit] = 0.0
+    got = dev.cpu().numpy()
+    # a corrected sample is one FP32 subtraction: half an ulp of a result below 16
+    assert np.max(np.abs(got[:, :n] - want)) <= 2.0 ** -21
+    np.testing.assert_array_equal(got[:, :n][:, hit], 0.0)
+    np.testing.assert_array_equal(got[:, n], x[:, n])
