@@ -297,13 +297,42 @@ int plan_direct(dd_plan* p, const Tiles& t) {
   l.form = kFormDirect;
   l.L = (int)(2 * kDirectTile);  // the widest wavefront tile (two sub-tiles)
   p->launch = l;
+  return DD_OK;
+}
+
+// The direct-read form's device table: every channel's delays, the last trial's in the padding.
+void table_direct(dd_plan* p) {
+  const int32_t nchan = p->nchan, ndm = p->ndm;
   p->dev_table.assign((size_t)nchan * p->ndm_pad, 0);
   for (int32_t c = 0; c < nchan; ++c) {
     const int32_t* row = &p->delays[(size_t)c * ndm];
     int32_t* drow = &p->dev_table[(size_t)c * p->ndm_pad];
     for (int32_t d = 0; d < p->ndm_pad; ++d) drow[d] = row[d < ndm ? d : ndm - 1];
   }
-  return DD_OK;
+}
+
+// The LDS form's device table: per (channel, trial) the LDS byte offset of the trial's first
+// 4-sample chunk inside the channel slot: relative delay k to the group's first trial is read
+// from copy m = k & 3 at word k - m; then [ngroups][nchan] the groups' first delays.
+void table_lds(dd_plan* p) {
+  const int32_t nchan = p->nchan, ndm = p->ndm;
+  p->dev_table.resize((size_t)nchan * p->ndm_pad + (size_t)p->ngroups * nchan);
+  int32_t* gb = &p->dev_table[(size_t)nchan * p->ndm_pad];
+  for (int32_t c = 0; c < nchan; ++c) {
+    const int32_t* row = &p->delays[(size_t)c * ndm];
+    int32_t* drow = &p->dev_table[(size_t)c * p->ndm_pad];
+    for (int32_t gi = 0; gi < p->ngroups; ++gi) {
+      const int32_t base = row[gi * p->dms_per_group];
+      gb[(size_t)gi * nchan + c] = base;
+      for (int32_t j = 0; j < p->dms_per_group; ++j) {
+        const int32_t d = gi * p->dms_per_group + j;
+        const int32_t k = row[d < ndm ? d : ndm - 1] - base;
+        const int32_t m = k & 3;
+        // byte offset: 32-bit words for 16/32-bit input, bytes for 8-bit input
+        drow[d] = p->dtype == DD_U8 ? m * p->launch.L + (k - m) : 4 * (m * p->launch.L + (k - m));
+      }
+    }
+  }
 }
 
 // ------------------------------------------------------------------ shared-sum form
@@ -567,6 +596,7 @@ bool plan_shared(dd_plan* p, int64_t lds_cap) {
     tab[2 * (size_t)g] = (int32_t)first;
     tab[2 * (size_t)g + 1] = nst;
     if (tab.size() > ((size_t)1 << 29)) return false;
+    if (g == 0) tab.reserve(std::min((size_t)1 << 29, tab.size() * (size_t)ng / 4 * 5));
   }
   p->sh.on = true;
   p->sh.nw = nw;
@@ -669,24 +699,25 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
   p->delays.resize((size_t)nchan * ndm);
 
   // Eq. deltaTEq: x = ((k * DM) * (1/(f*f) - 1/(fr*fr))) / tsamp, round half away from zero.
+  // x is not negative (no frequency exceeds fmax) and grows with the trial, so the last one's
+  // bounds a channel's delays, and a conversion to an integer is its floor.
   const double inv_ref = 1.0 / (fmax * fmax);
-  int64_t maxd = 0;
+  int32_t maxd = 0;
   for (int32_t c = 0; c < nchan; ++c) {
     const double diff = 1.0 / (freq_mhz[c] * freq_mhz[c]) - inv_ref;
+    if (!(((kDm * dm[ndm - 1]) * diff) / tsamp_s < (double)std::numeric_limits<int32_t>::max() + 0.5)) {
+      delete p;
+      return dd::fail(DD_ERR_INVALID_ARG, "delay exceeds 2^31-1 samples");
+    }
+    int32_t* row = &p->delays[(size_t)c * ndm];
     for (int32_t d = 0; d < ndm; ++d) {
       const double x = ((kDm * dm[d]) * diff) / tsamp_s;
-      const double fl = std::floor(x);
-      const double r = fl + ((x - fl) >= 0.5 ? 1.0 : 0.0);
-      if (!(r <= (double)std::numeric_limits<int32_t>::max())) {
-        delete p;
-        return dd::fail(DD_ERR_INVALID_ARG, "delay exceeds 2^31-1 samples");
-      }
-      const int32_t v = (int32_t)r;
-      p->delays[(size_t)c * ndm + d] = v;
-      if (v > maxd) maxd = v;
+      const int32_t fl = (int32_t)x;
+      row[d] = fl + (x - (double)fl >= 0.5 ? 1 : 0);
     }
+    maxd = std::max(maxd, row[ndm - 1]);
   }
-  p->maxdelay = (int32_t)maxd;
+  p->maxdelay = maxd;
 
   if (direct) {
     const int rc = dd::plan_direct(p, t);
@@ -694,7 +725,7 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
       delete p;
       return rc;
     }
-    if (auto_form) dd::plan_shared(p, lds_cap);
+    if (!(auto_form && dd::plan_shared(p, lds_cap))) dd::table_direct(p);
     p->id = g_next_id.fetch_add(1);
     *out = p;
     return DD_OK;
@@ -770,27 +801,7 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
   p->ngroups = (ndm + p->dms_per_group - 1) / p->dms_per_group;
   p->ndm_pad = p->ngroups * p->dms_per_group;
   p->max_span = span;
-  // device table: per (channel, trial) the LDS byte offset of the trial's first 4-sample
-  // chunk inside the channel slot: relative delay k to the group's first trial is read
-  // from copy m = k & 3 at word k - m; then [ngroups][nchan] the groups' first delays
-  p->dev_table.resize((size_t)nchan * p->ndm_pad + (size_t)p->ngroups * nchan);
-  int32_t* gb = &p->dev_table[(size_t)nchan * p->ndm_pad];
-  for (int32_t c = 0; c < nchan; ++c) {
-    const int32_t* row = &p->delays[(size_t)c * ndm];
-    int32_t* drow = &p->dev_table[(size_t)c * p->ndm_pad];
-    for (int32_t gi = 0; gi < p->ngroups; ++gi) {
-      const int32_t base = row[gi * p->dms_per_group];
-      gb[(size_t)gi * nchan + c] = base;
-      for (int32_t j = 0; j < p->dms_per_group; ++j) {
-        const int32_t d = gi * p->dms_per_group + j;
-        const int32_t k = row[d < ndm ? d : ndm - 1] - base;
-        const int32_t m = k & 3;
-        // byte offset: 32-bit words for 16/32-bit input, bytes for 8-bit input
-        drow[d] = in_dtype == DD_U8 ? m * lg.L + (k - m) : 4 * (m * lg.L + (k - m));
-      }
-    }
-  }
-  if (auto_form) dd::plan_shared(p, lds_cap);
+  if (!(auto_form && dd::plan_shared(p, lds_cap))) dd::table_lds(p);
   p->id = g_next_id.fetch_add(1);
   *out = p;
   return DD_OK;
