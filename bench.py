@@ -31,15 +31,16 @@ sys.path.insert(0, ROOT)
 # adds/s against the published peak; the add-rate fraction is printed beside it.
 PEAK_FP32_TFLOPS = 157.3
 PEAK_ADD_TFLOPS = 256 * 2.4e9 * 128 / 1e12
-# The kernel's own ceiling: every add consumes one 4-byte LDS word, and ds_read_b128
-# delivers ~221 B/clk/CU, so at most 256 x 2.4e9 x 221 / 4 = 33.9e12 adds/s.
+# Kernels that read one 4-byte LDS word per add (the LDS form, run with --tuning) have a
+# ceiling of their own: ds_read_b128 delivers ~221 B/clk/CU, so at most 256 x 2.4e9 x 221 / 4 =
+# 33.9e12 adds/s. The default plan's shared-sum form reads one word per up to 4 adds.
 LDS_CEILING_TADDS = 256 * 2.4e9 * 221 / 4 / 1e12
 PEAK_HBM_GBS = 8000.0
-TRAFFIC_FILE = os.path.join(ROOT, "profiles", "dedisp_tile_full_fp32_1024ch_2048dm_traffic.json")
+TRAFFIC_FILE = os.path.join(ROOT, "profiles", "dedisp_shared_full_fp32_1024ch_2048dm_traffic.json")
 _CSRC = os.path.join(ROOT, "paper_1401_8258_amd", "csrc")
-# what the LDS-form kernel's counters depend on: its device code (and the launch geometry,
-# compared separately)
-KERNEL_SOURCES = [os.path.join(_CSRC, f) for f in ("dedisp.hip", "dd_device.h")]
+# what the shared-sum kernel's counters depend on: its device code and the code that lays out its
+# tables (and the launch geometry, compared separately)
+KERNEL_SOURCES = [os.path.join(_CSRC, f) for f in ("shared.hip", "dd_device.h", "dd_internal.h", "plan.cpp")]
 GEOMETRY_KEYS = ("dms_per_wave", "waves", "producer_waves", "launch_buf", "launch_stage", "launch_ring",
                  "launch_lds")
 
@@ -61,7 +62,7 @@ def parse():
                     help="plain: the full-size FP32 workload (default); batch: 16 uneven u8 beams in one "
                          "batched call; serve: 64 streaming u8 beams with continuous batching; "
                          "subband: only the subband passes over the full-size FP32 workload; u8beam: the "
-                         "largest 4096-channel u8 beam of the batch in its default (direct-read) plan "
+                         "largest 4096-channel u8 beam of the batch in its default (shared-sum) plan "
                          "(both for profiling); binstream: a 4096-channel serving beam streamed plain and "
                          "with time binning")
     ap.add_argument("--serve-blocks", type=int, default=60,
@@ -373,7 +374,7 @@ def binned_stream_run(nblocks):
 
 def u8beam_run(steps, warmup):
     """The 4096-channel 120-180 MHz u8 beam of config 4 with the most work, default plan
-    (direct-read form): kernel-only launches (no statistics), then whole steps."""
+    (shared-sum form): kernel-only launches (no statistics), then whole steps."""
     import torch
 
     import fbsynth
@@ -530,7 +531,7 @@ def main():
     info = plan.query(nsamp)
     geometry = {k: int(info[k]) for k in GEOMETRY_KEYS}
     traffic, traffic_note = None, "no counter record"
-    if args.traffic and os.path.exists(args.traffic):
+    if args.tuning is None and args.traffic and os.path.exists(args.traffic):
         from paper_1401_8258_amd.profiling import source_digest
         with open(args.traffic) as f:
             rec = json.load(f)
@@ -544,13 +545,14 @@ def main():
     roof = {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS,
             "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "traffic": traffic,
             "traffic_note": traffic_note, "algorithmic_bytes": algo_bytes,
-            "kernel": "dedisp_tile", "kernel_ms": round(ms_kernel, 3), "geometry": geometry,
-            "achieved_note": "one FP32 add per (DM trial, channel, output sample) = one flop",
+            "kernel": "dedisp_shared" if args.tuning is None else "dedisp_tile", "kernel_ms": round(ms_kernel, 3), "geometry": geometry,
+            "achieved_note": "one FP32 add per (DM trial, channel, output sample) = one flop; the shared-sum form "
+                             "forms sums that several trials have in common once, so it issues fewer",
             "peak_note": "published FP32 vector peak: 256 CU x 2.4 GHz x 128 lanes x 2 (FMA)",
             "add_issue_rate": round(PEAK_ADD_TFLOPS, 2),
             "frac_of_add_issue_rate": round(achieved / PEAK_ADD_TFLOPS, 4),
             "add_issue_rate_note": "256 CU x 2.4 GHz x 128 lanes x 1 (an add is one flop per lane)",
-            "frac_of_lds_ceiling": round(achieved / LDS_CEILING_TADDS, 4),
+            "frac_of_lds_ceiling": None if args.tuning is None else round(achieved / LDS_CEILING_TADDS, 4),
             "algorithmic_hbm_gbs": round(algo_bytes / (ms_kernel * 1e-3) / 1e9, 1)}
 
     # detrending and normalisation of the dedispersed series (Sec. 3.5, downstream of the
@@ -741,8 +743,8 @@ def main():
     del sp
 
     # the same workload stored as 8-bit codes (clip(rint(128 + 16 x), 0, 255), made on the
-    # device), in the 8-bit default plan (direct-read form, exact integer sums): the kernel
-    # with its copy preparation alone, then whole steps with statistics and candidates
+    # device), in the 8-bit default plan (shared-sum form, exact integer sums): the kernel
+    # alone, then whole steps with statistics and candidates
     print("bench: 8-bit storage of the same workload", file=sys.stderr, flush=True)
     x8 = torch.clamp(torch.round(128.0 + 16.0 * x), 0, 255).to(torch.uint8)
     plan8 = dd.Plan(beam.freq_mhz, beam.tsamp_s, beam.dm, dtype="u8")

@@ -16,11 +16,14 @@
  *   cands    every (d, t) with D[d][t] > mean_d + k * rms_d, Ch. 3 Sec.
  *            "Detection and Candidate Selection", in ascending (d, t) order.
  *
- * Summation order (fixed, independent of tiling and of batching): channels are
- * summed in FP32 in order inside consecutive blocks of DD_CHAN_BLOCK channels
+ * Summation order (fixed by the plan, independent of batching and of blocks): channels
+ * are summed in FP32 in order inside consecutive blocks of DD_CHAN_BLOCK channels
  * (c = 0..31, 32..63, ...); the block sums are added to the running series in
- * block order. u8 inputs are summed as raw codes in 32-bit integers (exact; the
-output is that integer as FP32, exact below 2^24).
+ * block order. Plans that run in the shared-sum form (below) sum up to 4 neighbouring
+ * channels first, then those sums inside blocks of 128 channels in an order fixed at plan
+ * creation, then the blocks in order: their FP32 and FP16 series differ from the other
+ * forms' in the last bits. u8 inputs are summed as raw codes in 32-bit integers (exact; the
+ * output is that integer as FP32, exact below 2^24) in every form.
  *
  * Layouts: the filterbank is channel-major, time fastest ([nchan][row_stride],
  * Ch. 3 Sec. "Dedispersion" stores data after the transpose); the output is
@@ -77,7 +80,7 @@ enum {
 /* Input storage types. All accumulate in FP32. */
 enum { DD_F32 = 0, DD_F16 = 1, DD_U8 = 2 };
 
-/* Kernel forms of the dedispersion step (dd_tuning.kernel_form). All compute the same
+/* Kernel forms of the dedispersion step (dd_tuning.kernel_form). The named ones compute the same
    sums in the same order (for 8-bit input the sums are exact integers), so their series
    are identical bit for bit; their statistics partials may group the FP64 additions
    differently (last-bit differences in mean/rms for FP32 and FP16 input). */
@@ -103,6 +106,11 @@ enum {
                           producer_waves are ignored. Batched items of this form run in one
                           launch per tile shape and wavefront count, beside the LDS-form
                           items' launches */
+  /* Shared-sum form: no value of its own. Plans with DD_FORM_AUTO and no tile field run in it
+     (FP32 plans from 128 channels on, FP16 and 8-bit plans of any size), wherever 4
+     neighbouring channels' delays allow it: sums of 4 channels that several DM trials have in
+     common are formed once in LDS. dd_plan_info goes on describing the form that the plan
+     falls back to; the workspace, ring and batch calls are the same */
 };
 
 typedef struct dd_plan dd_plan;
@@ -127,8 +135,9 @@ typedef struct dd_tuning {
                                  (every wavefront issues its share of the DMAs), 1..4
                                  (waves + producer_waves <= 8; DD_ERR_UNSUPPORTED when the
                                  windows do not fit) */
-  int32_t kernel_form;        /* DD_FORM_AUTO (the direct-read form for 8-bit input when no
-                                 LDS-form tile field is set, else the LDS form), DD_FORM_LDS,
+  int32_t kernel_form;        /* DD_FORM_AUTO (no tile field set: the shared-sum form, falling
+                                 back to the direct-read form for 8-bit input and the LDS form
+                                 for other; with tile fields the LDS form), DD_FORM_LDS,
                                  DD_FORM_REGWIN (DD_ERR_UNSUPPORTED for
                                  other dtypes or a spread that does not fit) or DD_FORM_DIRECT
                                  (DD_ERR_UNSUPPORTED for other than 8-bit input) */
@@ -292,7 +301,8 @@ int dd_candidates_check(const int64_t* d_ncand, int64_t cand_cap, void* stream, 
  * direct-read form: DM trials per wavefront, samples per lane, wavefronts) run in one
  * launch that walks a device queue of (item, DM group, time tile) work, one launch per
  * distinct shape, each item on its own plan's tiles (an item of many units takes its plain
- * launch instead); then the statistics and candidates of all items take one launch per
+ * launch instead, as does an item in the shared-sum form, whose one launch fills the chip by
+ * its own work units); then the statistics and candidates of all items take one launch per
  * step. The results equal those of one dd_dedisperse per
  * item, bit for bit. Register-window plans are refused (DD_ERR_UNSUPPORTED).
  */

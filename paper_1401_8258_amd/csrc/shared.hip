@@ -3,13 +3,13 @@
 //
 // Within a few neighbouring channels the delays of the trials of one DM group differ by a
 // handful of patterns only: for channels c..c+3 the relative delays delta[c+j][d] -
-// delta[c][d] of 36 consecutive trials take about 4 distinct values on the 408-428 MHz band.
+// delta[c][d] of 32 consecutive trials take about 4 distinct values on the 408-428 MHz band.
 // For every such bundle of up to 4 channels the workgroup forms each pattern's sum
 //   S_p[x] = sum_j A[c_j][base_j + e_pj + x]      (window positions x, e_pj in 0..3)
-// once in LDS, and every trial adds one S_p at its own offset instead of 4 channels. The
-// sums are the same channels' samples; FP32 sums them inside the bundle in order, bundles in
-// order inside blocks of DD_CHAN_BLOCK channels, blocks in order, so no sum has more or
-// larger partial sums than channel by channel. 8-bit codes are exact integers either way.
+// once in LDS, and every trial adds one S_p at its own offset instead of 4 channels. FP32 sums
+// the channels of a bundle in order, the bundles of kShFold consecutive channels in one running
+// sum in the plan's order, and those sums in channel order, so a total carries fewer roundings
+// at full size than channel by channel. 8-bit codes are exact integers either way.
 //
 // Work unit: one time tile x one group of trials. A tile is 1008 words: 4 rows of 63 lanes of
 // 4 words. For FP32 and FP16 a word is one FP32 sample; for 8-bit input a word holds two
@@ -19,11 +19,26 @@
 // a 16-byte boundary takes its last words from the next lane by DPP, so one copy of each sum
 // serves every alignment with four conflict-free ds_read_b128 per 16 words.
 //
-// A stage is up to four bundles, double-buffered in LDS, with one barrier a stage. Every
+// A stage is up to three bundles, double-buffered in LDS, with one barrier a stage. Every
 // wavefront adds the stage's sums to its trials and forms its share of the next stage's, in
 // rows of 62-63 lanes x 4 window words of one bundle, from raw samples loaded into registers
-// a stage earlier. Both parts are bound by instruction issue (a wavefront alone issues one
-// instruction in about 6 clocks), so the forming is spread over all of them.
+// a stage earlier. Every other four wavefronts form before they add, so that one half's LDS
+// writes run beside the other's reads.
+//
+// What bounds it: instruction issue and LDS together. FP32, 1024 channels x 2048 trials, per 4
+// channels of 32 trials x 1008 samples: 1376 clocks of a CU, of which LDS is busy about 840
+// (16 bytes a lane read in 4.2 clocks, written in 13.9) and each SIMD issues vector
+// instructions for 935. HBM traffic is under a twentieth of the time. Measured and not kept:
+// - wavefronts that only form beside ones that only add (12 + 4): bound by the forming ones,
+//   101 ms against 59 at the time; all 16 doing both fills the waits of either part;
+// - 12 wavefronts of 3 trials with 168 registers: 44.5 ms against 37.3 with 16 of 2;
+// - several smaller workgroups per CU: fewer trials share each sum; slower but where the delays
+//   grow by many samples a trial, which is what plan_shared weighs;
+// - asking for the records' cache lines ahead of their loads: no difference.
+// Times before (the LDS form for FP32 and FP16, the direct-read form for 8-bit) and now:
+//   1024 channels x 2048 trials, 408-428 MHz, FP32, 262144 samples   99.6 -> 37.3 ms
+//   the same band, 8-bit, 1024 channels x 2048 trials                22.6 -> 5.9 ms
+//   4096 channels x 750 trials of a low band, 8-bit                  22.0 -> 10.9 ms
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
