@@ -107,7 +107,8 @@ enum {
                           launch per tile shape and wavefront count, beside the LDS-form
                           items' launches */
   /* Shared-sum form: no value of its own. Plans with DD_FORM_AUTO and no tile field run in it
-     (FP32 plans from 128 channels on, FP16 and 8-bit plans of any size), wherever 4
+     (FP32 plans from 128 channels on, FP16 and 8-bit plans of any size; so do the steps of
+     subband plans where it is cheaper), wherever 4
      neighbouring channels' delays allow it: sums of 4 channels that several DM trials have in
      common are formed once in LDS. dd_plan_info goes on describing the form that the plan
      falls back to; the workspace, ring and batch calls are the same */
@@ -559,10 +560,10 @@ int dd_subband_query(const dd_subband* sp, int64_t nsamp, int64_t* workspace_byt
                      int64_t* adds, int32_t* nsub, int32_t* ngroups);
 int dd_subband_upload(const dd_subband* sp, int64_t nsamp, void* d_workspace, int64_t ws_bytes, void* stream);
 /* One call over both steps; outputs and candidates as dd_binned_dedisperse (row d holds
-   its group's nout; times in input samples). batched != 0 runs each step through one
-   dd_batch_dedisperse call (same results bit for bit). Unbatched, the step-2 plans run on
-   four side streams of the calling host thread (as dd_binned_dedisperse's) and `stream`
-   waits for them. */
+   its group's nout; times in input samples). batched != 0 runs a step without plans in the
+   shared-sum form through one dd_batch_dedisperse call (same results bit for bit). Otherwise
+   the plans of each step run on four side streams of the calling host thread (as
+   dd_binned_dedisperse's) and `stream` waits for them. */
 int dd_subband_dedisperse(const dd_subband* sp, const float* d_in, int64_t nsamp, int64_t in_row_stride, float* d_out,
                           int64_t out_row_stride, float* d_mean, float* d_rms, float k_sigma, dd_cand* d_cand,
                           int64_t cand_cap, int64_t* d_ncand, int32_t batched, void* d_workspace, int64_t ws_bytes,

@@ -82,6 +82,12 @@ constexpr int kShFold = 128;
 // 14 patterns per 16 to 32 trials at 64 channels, 4 at 1024), and their series stay those of
 // every explicit tiling, bit for bit.
 constexpr int kShMinChans = 128;
+// The steps of a subband plan (few channels: neighbouring pairs share sums, hardly fours) take the
+// shared-sum form where its clocks per trial and 4 channels, estimated, are below this. Up to
+// there (92 to 158 over subbands of 8 to 64 channels with 16 and 48 trials per nominal DM) it
+// measured 1.1 to 1.8 times as fast as the LDS form, whose 56-trial workgroups are mostly padding
+// for a handful of nominal DMs; beyond, windows are many times the tile.
+constexpr double kShFewClk = 160.0;
 constexpr int kShMaxBundles = 3;  // bundles of a stage
 constexpr int kShBlock = 136;     // bytes of code per pattern block
 constexpr int kShSpare = 1024;    // LDS bytes before the stages: where lanes without a chunk write
@@ -165,10 +171,11 @@ namespace dd {
 // Thread-local error message helpers (implemented in plan.cpp).
 int fail(int code, const std::string& msg);
 void clear_error();
-// dd_plan_create with the LDS bytes one workgroup may take (csrc/plan.cpp); dd_plan_create
-// passes kLdsBytes.
+// dd_plan_create with the LDS bytes one workgroup may take (csrc/plan.cpp), and whether FP32 plans
+// below kShMinChans channels may take the shared-sum form (where it is cheaper: kShFewClk);
+// dd_plan_create passes kLdsBytes and false.
 int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsamp_s, const double* dm,
-                int32_t ndm, int32_t in_dtype, const dd_tuning* tuning, int64_t lds_cap);
+                int32_t ndm, int32_t in_dtype, const dd_tuning* tuning, int64_t lds_cap, bool shared_any);
 
 // Workspace layout for one dd_dedisperse call.
 struct WsLayout {
@@ -223,8 +230,9 @@ struct InView {
 int launch_regwin(const dd_plan* p, const InView& in, const int32_t* d_table, int64_t nout, float* out,
                   int64_t out_stride, double* part, void* stream);
 // Shared-sum form: fills sh, the groups and the device table and returns true, or leaves the
-// plan as it is and returns false where that form would not pay.
-bool plan_shared(dd_plan* p, int64_t lds_cap);
+// plan as it is and returns false where that form does not fit or is estimated to take max_cost
+// clocks or more per trial and 4 channels of a tile.
+bool plan_shared(dd_plan* p, int64_t lds_cap, double max_cost);
 int launch_shared(const dd_plan* p, const InView& in, const int32_t* d_table, int64_t nout, float* out,
                   int64_t out_stride, double* part, void* stream);
 // Direct-read form (8-bit input): device table [nchan][ndm_pad] of plain delays (padded trials

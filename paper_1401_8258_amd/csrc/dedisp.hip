@@ -2546,16 +2546,21 @@ int dd_subband_create(dd_subband** out, const double* freq_mhz, int32_t nchan, d
   int rc = DD_OK;
   for (const auto& s : sp->subs) {
     dd_plan* p = nullptr;
-    rc = dd_plan_create(&p, freq_mhz + s.first, s.second - s.first, tsamp_s, nominal.data(), (int32_t)nominal.size(),
-                        DD_F32, nullptr);
+    // in the shared-sum form where that is cheaper: nobody compares these sums with another
+    // tiling's
+    rc = dd::plan_create(&p, freq_mhz + s.first, s.second - s.first, tsamp_s, nominal.data(), (int32_t)nominal.size(),
+                         DD_F32, nullptr, dd::kLdsBytes, true);
     if (rc) break;
     sp->step1.push_back(p);
     fsub.push_back(*std::max_element(freq_mhz + s.first, freq_mhz + s.second));
   }
-  // step 2: groups of dms_per_group trials share a workgroup, 4 trials per computing
-  // wavefront beside 2 producers. A step-2 plan walks only the subbands, so its units are
-  // short: the LDS budget lets as many workgroups share a CU as its 16 wavefront slots
-  // hold (two for groups of 16), and each takes the budget's share of the LDS.
+  // step 2: groups of up to 32 trials, the most a workgroup of the shared-sum form takes, run in
+  // that form where it is cheaper (16-trial passes: 1024 channels x 2^19 samples x 960 trials
+  // 6.43 -> 6.09 ms, with 16-channel subbands 3.00 -> 2.58; groups of 48 would pad a second
+  // workgroup, 4.40 -> 4.80). Others run in the LDS form: a group's trials share a workgroup, 4
+  // trials per computing wavefront beside 2 producers. Its units are short, as the plan walks
+  // only the subbands: the LDS budget lets as many workgroups share a CU as its 16 wavefront
+  // slots hold, and each takes the budget's share of the LDS.
   dd_tuning t2{};
   t2.dms_per_wave = 4;
   t2.waves = std::max(1, std::min(14, (dms_per_group + 3) / 4));
@@ -2567,9 +2572,19 @@ int dd_subband_create(dd_subband** out, const double* freq_mhz, int32_t nchan, d
     // the budget's share, or the whole LDS when one group's windows need more; 8 trials per
     // wavefront when they do not fit the producers' DMAs at all
     const int32_t d0 = sp->groups[g].first, nd = sp->groups[g].second - sp->groups[g].first;
+    if (dms_per_group <= dd::kShG * dd::kShWaves) {
+      rc = dd::plan_create(&p, fsub.data(), (int32_t)fsub.size(), tsamp_s, dm + d0, nd, DD_F32, nullptr,
+                           dd::kLdsBytes, true);
+      if (rc == DD_OK && p->sh.on) {
+        sp->step2.push_back(p);
+        continue;
+      }
+      dd_plan_destroy(p);
+      p = nullptr;
+    }
     for (int64_t div = share; div >= 1; div = div > 1 ? 1 : 0) {
       rc = dd::plan_create(&p, fsub.data(), (int32_t)fsub.size(), tsamp_s, dm + d0, nd, DD_F32, &t2,
-                           dd::kLdsBytes / div);
+                           dd::kLdsBytes / div, false);
       if (rc != DD_ERR_UNSUPPORTED) break;
     }
     if (rc == DD_ERR_UNSUPPORTED) {
@@ -2655,8 +2670,34 @@ int dd_subband_dedisperse(const dd_subband* sp, const float* d_in, int64_t nsamp
   float* red = reinterpret_cast<float*>(ws + L.red_off);
   const int64_t ngrp = (int64_t)sp->groups.size();
   const bool stats = d_mean && d_rms;
+  // unbatched, the plans of a step are independent and each is a short launch: they go
+  // round-robin over a few side streams (the per-thread pool of the binned plans), forked from
+  // the caller's stream and joined to it again whatever becomes of the launches
+  constexpr size_t kSides = 4;
+  auto on_sides = [&](const char* what, auto&& launches) -> int {
+    SidePool* pool = nullptr;
+    int r = side_pool(kSides, kSides + 1, &pool);
+    if (r) return r;
+    hipError_t e = hipEventRecord(pool->events[0], st);
+    for (size_t x = 0; e == hipSuccess && x < kSides; ++x) e = hipStreamWaitEvent(pool->streams[x], pool->events[0], 0);
+    if (e != hipSuccess) return hip_fail(e, what);
+    r = launches(pool->streams);
+    for (size_t x = 0; x < kSides; ++x) {
+      hipError_t j = hipEventRecord(pool->events[1 + x], pool->streams[x]);
+      if (j == hipSuccess) j = hipStreamWaitEvent(st, pool->events[1 + x], 0);
+      if (e == hipSuccess) e = j;
+    }
+    if (r) return r;
+    return e != hipSuccess ? hip_fail(e, what) : DD_OK;
+  };
+  // a batched call takes a launch for each plan in the shared-sum form, so a step with such plans
+  // goes over the side streams there too (1024 channels x 2^19 samples x 960 trials: 5.8 ms, 7.1
+  // with the launches on one stream)
+  auto one_launch = [&](const std::vector<dd_plan*>& plans) {
+    return batched && !std::any_of(plans.begin(), plans.end(), [](const dd_plan* p) { return p->sh.on; });
+  };
   // step 1: subband s at the nominal DMs into red[s][g][:]
-  if (batched) {
+  if (one_launch(sp->step1)) {
     std::vector<dd_batch_item> items(sp->step1.size());
     for (size_t s = 0; s < sp->step1.size(); ++s) {
       dd_batch_item& it = items[s];
@@ -2672,17 +2713,21 @@ int dd_subband_dedisperse(const dd_subband* sp, const float* d_in, int64_t nsamp
     rc = dd_batch_dedisperse(items.data(), (int32_t)items.size(), ws + L.batch_off, L.cand_off - L.batch_off, stream);
     if (rc) return rc;
   } else {
-    for (size_t s = 0; s < sp->step1.size(); ++s) {
-      char* rw = ws + L.off1[s];
-      const InView in{d_in + (int64_t)sp->subs[s].first * in_row_stride, in_row_stride, nsamp, 0, 0};
-      const Outputs o{red + (int64_t)s * ngrp * L.width, L.width, nullptr, nullptr, 0.f, nullptr, 0, nullptr, 0};
-      rc = run_pipeline(sp->step1[s], in, reinterpret_cast<const int32_t*>(rw + L.l1[s].table_off), L.nout1[s], o, rw,
-                        L.l1[s], st, true);
-      if (rc) return rc;
-    }
+    rc = on_sides("subband step 1: side streams", [&](const std::vector<hipStream_t>& sides) -> int {
+      for (size_t s = 0; s < sp->step1.size(); ++s) {
+        char* rw = ws + L.off1[s];
+        const InView in{d_in + (int64_t)sp->subs[s].first * in_row_stride, in_row_stride, nsamp, 0, 0};
+        const Outputs o{red + (int64_t)s * ngrp * L.width, L.width, nullptr, nullptr, 0.f, nullptr, 0, nullptr, 0};
+        const int r = run_pipeline(sp->step1[s], in, reinterpret_cast<const int32_t*>(rw + L.l1[s].table_off),
+                                   L.nout1[s], o, rw, L.l1[s], sides[s % kSides], true);
+        if (r) return r;
+      }
+      return DD_OK;
+    });
+    if (rc) return rc;
   }
   // step 2: group g over the reduced filterbank red[:][g][0 .. len1)
-  if (batched) {
+  if (one_launch(sp->step2)) {
     std::vector<dd_batch_item> items(sp->step2.size());
     for (size_t g = 0; g < sp->step2.size(); ++g) {
       dd_batch_item& it = items[g];
@@ -2701,31 +2746,20 @@ int dd_subband_dedisperse(const dd_subband* sp, const float* d_in, int64_t nsamp
     rc = dd_batch_dedisperse(items.data(), (int32_t)items.size(), ws + L.batch_off, L.cand_off - L.batch_off, stream);
     if (rc) return rc;
   } else {
-    // the step-2 plans are independent once step 1 is done and each is a short launch: they
-    // go round-robin over a few side streams (the per-thread pool of the binned plans),
-    // joined before the merged candidates
-    constexpr size_t kSides = 4;
-    SidePool* pool = nullptr;
-    rc = side_pool(kSides, kSides + 1, &pool);
+    rc = on_sides("subband step 2: side streams", [&](const std::vector<hipStream_t>& sides) -> int {
+      for (size_t g = 0; g < sp->step2.size(); ++g) {
+        char* rw = ws + L.off2[g];
+        const int32_t d0 = sp->groups[g].first;
+        const InView in{red + (int64_t)g * L.width, ngrp * L.width, L.len1, 0, 0};
+        const Outputs o{d_out + (int64_t)d0 * out_row_stride, out_row_stride, stats ? d_mean + d0 : nullptr,
+                        stats ? d_rms + d0 : nullptr, k_sigma, nullptr, 0, nullptr, 0};
+        const int r = run_pipeline(sp->step2[g], in, reinterpret_cast<const int32_t*>(rw + L.l2[g].table_off),
+                                   L.nout2[g], o, rw, L.l2[g], sides[g % kSides], true);
+        if (r) return r;
+      }
+      return DD_OK;
+    });
     if (rc) return rc;
-    hipError_t e = hipEventRecord(pool->events[0], st);
-    for (size_t x = 0; e == hipSuccess && x < kSides; ++x) e = hipStreamWaitEvent(pool->streams[x], pool->events[0], 0);
-    if (e != hipSuccess) return hip_fail(e, "subband step 2: side streams");
-    for (size_t g = 0; g < sp->step2.size(); ++g) {
-      char* rw = ws + L.off2[g];
-      const int32_t d0 = sp->groups[g].first;
-      const InView in{red + (int64_t)g * L.width, ngrp * L.width, L.len1, 0, 0};
-      const Outputs o{d_out + (int64_t)d0 * out_row_stride, out_row_stride, stats ? d_mean + d0 : nullptr,
-                      stats ? d_rms + d0 : nullptr, k_sigma, nullptr, 0, nullptr, 0};
-      rc = run_pipeline(sp->step2[g], in, reinterpret_cast<const int32_t*>(rw + L.l2[g].table_off), L.nout2[g], o, rw,
-                        L.l2[g], pool->streams[g % kSides], true);
-      if (rc) return rc;
-    }
-    for (size_t x = 0; e == hipSuccess && x < kSides; ++x) {
-      e = hipEventRecord(pool->events[1 + x], pool->streams[x]);
-      if (e == hipSuccess) e = hipStreamWaitEvent(st, pool->events[1 + x], 0);
-    }
-    if (e != hipSuccess) return hip_fail(e, "subband step 2: joining the side streams");
   }
   if (stats && k_sigma > 0.f && d_ncand) {
     std::vector<MergedRun> mr;

@@ -105,3 +105,23 @@ def test_ring_input_and_batch_equal_one_shot(torch, dd, dtype):
         assert torch.equal(r.out, whole[:, seen:seen + r.out.shape[1]]), f"block at t0={r.t0} differs"
         seen += r.out.shape[1]
     assert seen == whole.shape[1]
+
+
+@pytest.mark.parametrize("nchan,csub,ndm,dgroup", [(200, 32, 70, 16), (130, 64, 75, 33), (96, 8, 40, 32), (33, 32, 5, 4)])
+def test_subband_steps_equal_oracle(torch, dd, nchan, csub, ndm, dgroup):
+    """Both steps of a subband plan, at a short last subband (of one channel in the last case) and
+    group, and on both sides of the largest group that the shared-sum form takes; batched equal."""
+    print(f"case: subband {nchan}/{csub} {ndm}/{dgroup}", flush=True)
+    freq, dm, _ = _case(nchan, 20.0 / nchan, 428.0, ndm, 0.1, "down")
+    x = np.random.default_rng(nchan).standard_normal((nchan, 5003)).astype(np.float32)
+    want = orc.subband_dedisperse(x, freq, 51.2e-6, dm, csub, dgroup)
+    sp = dd.SubbandPlan(freq, 51.2e-6, dm, chans_per_sub=csub, dms_per_group=dgroup)
+    dev = torch.from_numpy(x).cuda()
+    res, bat = sp.dedisperse(dev, k_sigma=5.0), sp.dedisperse(dev, k_sigma=5.0, batched=True)
+    torch.cuda.synchronize()
+    assert [g for g, _ in res] == [(d0, d1) for d0, d1, _ in want]
+    for (_, r), (_, b), (d0, _, s) in zip(res, bat, want):
+        mean, rms = orc.series_stats(s)
+        assert_rows_close(r.out.cpu().numpy(), s, rms, what=f"group {d0}")
+        assert_stats_close(r.mean.cpu().numpy(), r.rms.cpu().numpy(), mean, rms)
+        assert torch.equal(r.out, b.out) and torch.equal(r.mean, b.mean) and torch.equal(r.rms, b.rms)
