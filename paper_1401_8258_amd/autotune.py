@@ -15,6 +15,11 @@ beam's own best (a batched call runs every beam on its own tiles, one launch per
 shape), or on request each beam's best under the one count that minimises their summed
 time (fewer launches). The timer is a parameter (``time_plan`` on the
 device by default). Results are cached by (nchan, ndm, dtype, nsamp, DM list hash).
+
+The tuner chooses among the forms that have tiles. A plan without a tuning runs in the
+shared-sum form, which has none and is faster than every tiling on the beams measured
+(1024-channel FP32 39 against 100 ms, 8-bit 6.6 against 22.8 ms), so tune only plans that must
+run in one of these forms.
 """
 from __future__ import annotations
 
