@@ -88,6 +88,14 @@ constexpr int kShMinChans = 128;
 // measured 1.1 to 1.8 times as fast as the LDS form, whose 56-trial workgroups are mostly padding
 // for a handful of nominal DMs; beyond, windows are many times the tile.
 constexpr double kShFewClk = 160.0;
+// An 8-bit plan takes the shared-sum form where its estimated clocks per trial (with both forms'
+// padding) and 4 channels are below this, else the direct-read form. Wide channels and coarse
+// trials at low frequencies leave one channel a bundle and long windows: at 290 to 410 clocks
+// (512 to 4096 channels of 120-180 MHz, steps of 0.2 and 0.25) the shared-sum form took 1.25 to
+// 1.6 times the direct-read form's time, at 170 to 190 1.02 to 1.09 times, at 115 0.81, at 92
+// (4096 channels, steps of 0.05) 0.5 and at 49 (408-428 MHz) 0.26. FP32 and FP16 need no such
+// rule: the LDS form loses as much there (never faster on the same beams, 1.4 to 14 times slower).
+constexpr double kShDirectClk = 140.0;
 constexpr int kShMaxBundles = 3;  // bundles of a stage
 constexpr int kShBlock = 136;     // bytes of code per pattern block
 constexpr int kShSpare = 1024;    // LDS bytes before the stages: where lanes without a chunk write

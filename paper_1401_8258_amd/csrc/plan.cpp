@@ -492,6 +492,8 @@ bool plan_shared(dd_plan* p, int64_t lds_cap, double max_cost) {
   const int nw = maxw / best_div, n = G * nw;
   const int64_t cap = (lds_cap / best_div - kShSpare) / 2 / 256 * 256;
   const int ng = (ndm + n - 1) / n;
+  // ndm_pad is still the direct-read form's (kShDirectClk)
+  if (p->dtype == DD_U8 && !(best * ((double)ng * n) < kShDirectClk * p->ndm_pad)) return false;
   const int ints = sh_stage_ints(nw);
   std::vector<int32_t> tab((size_t)(2 * ng + 63) / 64 * 64 + (size_t)ints, 0);
   int64_t max_reach = 0;
