@@ -20,9 +20,9 @@
  * are summed in FP32 in order inside consecutive blocks of DD_CHAN_BLOCK channels
  * (c = 0..31, 32..63, ...); the block sums are added to the running series in
  * block order. Plans that run in the shared-sum form (below) sum up to 4 neighbouring
- * channels first, then those sums inside blocks of 128 channels in an order fixed at plan
- * creation, then the blocks in order: their FP32 and FP16 series differ from the other
- * forms' in the last bits. u8 inputs are summed as raw codes in 32-bit integers (exact; the
+ * channels first, then those sums inside blocks of 32 to 128 channels in an order fixed at
+ * plan creation, then the blocks in order: their FP32 and FP16 series differ from the other
+ * forms' in the last bits, and round no worse. u8 inputs are summed as raw codes in 32-bit integers (exact; the
  * output is that integer as FP32, exact below 2^24) in every form.
  *
  * Layouts: the filterbank is channel-major, time fastest ([nchan][row_stride],

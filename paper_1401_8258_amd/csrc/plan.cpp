@@ -343,7 +343,7 @@ constexpr int kShMaxTrials = 2 * 16;  // trials of a group
 
 // One bundle of 1..4 consecutive channels for one group of trials.
 struct Bundle {
-  int m, np, slot, rows;  // channels, patterns, bytes of a pattern's sums, rows
+  int c0, m, np, slot, rows;  // lowest channel, channels, patterns, bytes of a pattern's sums, rows
   int records() const { return rows * ((np + kShRecPat - 1) / kShRecPat); }
   int32_t off[4], chan;   // window starts; the first channel
   bool down;              // the channels run down from it
@@ -374,6 +374,7 @@ bool make_bundle(const dd_plan* p, int c0, int m, int d0, int n, int64_t cap, Bu
   const int32_t k0 = row[0][0];
   const int64_t chunks = (int64_t)(row[0][nd - 1] - k0) / 4 + 4 * 63 + 1;
   if (16 * chunks > cap) return false;
+  b->c0 = c0;
   b->m = m;
   b->slot = (int)(16 * chunks);
   b->rows = (int)((chunks + sh_row_chunks(p->dtype) - 1) / sh_row_chunks(p->dtype));
@@ -451,6 +452,43 @@ bool bundle_quad(const dd_plan* p, int c0, int c1, int d0, int n, int64_t cap, s
   return true;
 }
 
+// The FP32 additions of a series, by the channels that their results hold: a result's rounding
+// error grows as its size, so the variance of a total's error as the number of channels (noise
+// about zero) up to its square (noise on a level) summed over the additions.
+struct Adds {
+  double lin = 0, sq = 0;
+  void add(int n) {
+    lin += n;
+    sq += (double)n * n;
+  }
+  bool no_more_than(const Adds& o) const { return lin <= o.lin && sq <= o.sq; }
+};
+
+// Channels [c0, c1) in blocks of DD_CHAN_BLOCK, channel by channel, joining a total of the c0
+// channels before them.
+Adds by_channel(int c0, int c1) {
+  Adds a;
+  for (int b = c0; b < c1; b += DD_CHAN_BLOCK) {
+    const int e = std::min(c1, b + DD_CHAN_BLOCK);
+    for (int k = 2; k <= e - b; ++k) a.add(k);
+    if (b) a.add(e);
+  }
+  return a;
+}
+
+// The same channels as one block of these bundles.
+Adds by_bundle(int c0, const std::vector<Bundle>& v, const std::vector<int>& order) {
+  Adds a;
+  int n = 0;
+  for (int i : order) {
+    for (int k = 2; k <= v[(size_t)i].m; ++k) a.add(k);
+    if (n) a.add(n + v[(size_t)i].m);
+    n += v[(size_t)i].m;
+  }
+  if (c0) a.add(c0 + n);
+  return a;
+}
+
 }  // namespace
 
 // Device table: per group {offset, stages}, then the stages' records (dd_internal.h).
@@ -510,24 +548,30 @@ bool plan_shared(dd_plan* p, int64_t lds_cap, double max_cost) {
     int nst = 0;
     over.clear();
     links.clear();
-    for (int f0 = 0; f0 < nchan; f0 += fold) {
-      const int f1 = std::min(nchan, f0 + fold);
-      v.clear();
+    v.clear();
+    for (int f0 = 0, f1 = 0; f0 < nchan; f0 = f1) {
       double cost = 0;
-      for (int q = f0; q < f1; q += 4)
+      f1 = std::min(nchan, f0 + fold);
+      for (int q = v.empty() ? f0 : v.back().c0 + v.back().m; q < f1; q += 4)
         if (!bundle_quad(p, q, std::min(f1, q + 4), g * n, n, cap, &v, &cost)) return false;
-      // bundles of like pattern counts share a stage: its slowest row sets its time
-      order.resize(v.size());
-      for (size_t i = 0; i < v.size(); ++i) order[i] = (int)i;
-      std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return v[(size_t)a].np < v[(size_t)b].np; });
-      for (size_t i = 0; i < v.size();) {
+      // the block's length: the FP32 additions of a longer one may round worse than channel by
+      // channel (those of DD_CHAN_BLOCK channels never do: its partial sums are among the others')
+      for (int len = fold;; len /= 2) {
+        f1 = std::min(nchan, f0 + len);
+        order.clear();
+        for (size_t i = 0; i < v.size() && v[i].c0 < f1; ++i) order.push_back((int)i);
+        // bundles of like pattern counts share a stage: its slowest row sets its time
+        std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return v[(size_t)a].np < v[(size_t)b].np; });
+        if (p->dtype == DD_U8 || len <= DD_CHAN_BLOCK || by_bundle(f0, v, order).no_more_than(by_channel(f0, f1))) break;
+      }
+      for (size_t i = 0; i < order.size();) {
         // up to kShMaxBundles bundles that fit half the LDS share: as many as leave the fewest
         // wavefronts without a row in the last round of rows
         size_t e = i + 1;
         int64_t bytes = 0;
         int nrec = 0;
         double best_fill = 0;
-        for (size_t k = i; k < v.size() && k - i < (size_t)kShMaxBundles; ++k) {
+        for (size_t k = i; k < order.size() && k - i < (size_t)kShMaxBundles; ++k) {
           const Bundle& b = v[(size_t)order[k]];
           bytes += b.bytes();
           nrec += b.records();
@@ -549,7 +593,7 @@ bool plan_shared(dd_plan* p, int64_t lds_cap, double max_cost) {
               rec[G * q + t] = tr & ~15;
               rec[6] |= (tr & 3) << (2 * (G * q + t));
             }
-          rec[7] = (G * nb - 1) | (e == v.size() ? 256 : 0);
+          rec[7] = (G * nb - 1) | (e == order.size() ? 256 : 0);
         }
         // the rows, those of many patterns in parts and first, round the wavefronts
         int k = 0;
@@ -594,6 +638,7 @@ bool plan_shared(dd_plan* p, int64_t lds_cap, double max_cost) {
         ++nst;
         i = e;
       }
+      v.erase(v.begin(), v.begin() + (std::ptrdiff_t)order.size());
     }
     tab.resize(tab.size() + (size_t)kShPad * ints, 0);
     const int32_t after = (int32_t)(tab.size() - first);

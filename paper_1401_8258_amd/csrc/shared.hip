@@ -7,9 +7,10 @@
 // For every such bundle of up to 4 channels the workgroup forms each pattern's sum
 //   S_p[x] = sum_j A[c_j][base_j + e_pj + x]      (window positions x, e_pj in 0..3)
 // once in LDS, and every trial adds one S_p at its own offset instead of 4 channels. FP32 sums
-// the channels of a bundle in order, the bundles of kShFold consecutive channels in one running
-// sum in the plan's order, and those sums in channel order, so a total carries fewer roundings
-// at full size than channel by channel. 8-bit codes are exact integers either way.
+// the channels of a bundle in order, the bundles of a block of up to kShFold consecutive channels
+// in one running sum in the plan's order, and those sums in channel order; the plan chooses the
+// blocks so that a total rounds no worse than channel by channel (dd_internal.h). 8-bit codes are
+// exact integers either way.
 //
 // Work unit: one time tile x one group of trials. A tile is 1008 words: 4 rows of 63 lanes of
 // 4 words. For FP32 and FP16 a word is one FP32 sample; for 8-bit input a word holds two
@@ -422,7 +423,7 @@ __device__ __forceinline__ void add_stage(uint32_t (&acc)[2][16], const Adds& k,
   DD_STAGE("v_add_u32");
 }
 
-// Blocks of kShFold channels (FP32) or 256 channels (8-bit codes: 255 x 256 < 2^16) close into
+// Blocks of up to kShFold channels (FP32) or 256 channels (8-bit codes: 255 x 256 < 2^16) close into
 // the running totals.
 __device__ __forceinline__ void fold(float (&tot)[16], float (&acc)[16]) {
 #pragma unroll
