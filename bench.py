@@ -41,8 +41,6 @@ _CSRC = os.path.join(ROOT, "paper_1401_8258_amd", "csrc")
 # what the shared-sum kernel's counters depend on: its device code and the code that lays out its
 # tables (and the launch geometry, compared separately)
 KERNEL_SOURCES = [os.path.join(_CSRC, f) for f in ("shared.hip", "dd_device.h", "dd_internal.h", "plan.cpp")]
-GEOMETRY_KEYS = ("dms_per_wave", "waves", "producer_waves", "launch_buf", "launch_stage", "launch_ring",
-                 "launch_lds")
 
 
 def parse():
@@ -277,8 +275,8 @@ def batch_run(reps):
     for p, x, o in zip(plans, xs, outs):
         ms = timed(lambda: dd.batch_dedisperse([(p, x)], k_sigma=6.0, cand_cap=1 << 16, outputs=[o]))
         nout = x.shape[1] - p.maxdelay
-        per_beam.append({"nchan": p.nchan, "ndm": p.ndm, "nout": nout, "form": p.form, "tiles": list(p.tiles[:2]),
-                         "ms": round(ms, 3), "adds_per_s": p.ndm * p.nchan * nout / (ms * 1e-3)})
+        per_beam.append({"nchan": p.nchan, "ndm": p.ndm, "nout": nout, "form": p.kernel["form"],
+                         "tiles": [p.kernel["dms_per_wave"], p.kernel["waves"]], "ms": round(ms, 3), "adds_per_s": p.ndm * p.nchan * nout / (ms * 1e-3)})
     ms_single = sum(b["ms"] for b in per_beam)
     trials_samples = sum(p.ndm * (x.shape[1] - p.maxdelay) for p, x in jobs)
     adds = sum(p.ndm * p.nchan * (x.shape[1] - p.maxdelay) for p, x in jobs)
@@ -336,7 +334,8 @@ def binned_stream_run(nblocks):
     e1.record(stream)
     torch.cuda.synchronize()
     ms_plain = e0.elapsed_time(e1) / nblocks
-    res["plain"] = {"ring_bytes": int(st.ring.numel()), "maxdelay": plan.maxdelay, "form": plan.form,
+    res["plain"] = {"ring_bytes": int(st.ring.numel()), "maxdelay": plan.maxdelay,
+                    "form": plan.kernel["form"],
                     "ms_per_block": round(ms_plain, 3), "adds_per_block": plan.ndm * plan.nchan * block}
     del st
     torch.cuda.empty_cache()
@@ -360,7 +359,7 @@ def binned_stream_run(nblocks):
     adds_b = sum((sg.d1 - sg.d0) * bp.freq.size * (block >> sg.log2) for sg in bp.segments)
     res["binned"] = {"ring_bytes": bs.ring_bytes, "max_log2": 4, "dm_diag": round(bp.dm_diag, 4),
                      "runs": [{"factor": 1 << sg.log2, "ndm": sg.d1 - sg.d0, "maxdelay": sg.plan.maxdelay,
-                               "form": sg.plan.form} for sg in bp.segments],
+                               "form": kn["form"]} for sg, kn in zip(bp.segments, bp.kernels)],
                      "ms_per_block": round(ms_b, 3), "ms_per_block_unbatched": round(ms_by[False], 3),
                      "ms_per_block_batched": round(ms_by[True], 3) if True in ms_by else None,
                      "adds_per_block": adds_b}
@@ -406,7 +405,8 @@ def u8beam_run(steps, warmup):
     adds = plan.ndm * plan.nchan * nout
     return {"workload": f"u8 beam: {plan.nchan} ch 120-180 MHz, tsamp 81.92 us, nsamp {sp['nsamp']}, "
                         f"{plan.ndm} DMs step {sp['step']}, maxdelay {plan.maxdelay}",
-            "form": plan.form, "tiles": list(plan.tiles[:2]), "nout": nout, "adds": adds,
+            "form": plan.kernel["form"], "tiles": [plan.kernel["dms_per_wave"], plan.kernel["waves"]], "nout": nout,
+            "adds": adds,
             "adds_per_s_prep_and_kernel": adds / (res["prep_and_kernel_ms"] * 1e-3), **res}
 
 
@@ -528,10 +528,10 @@ def main():
 
     adds = beam.ndm * beam.nchan * nout
     achieved = adds / (ms_kernel * 1e-3) / 1e12
-    info = plan.query(nsamp)
-    geometry = {k: int(info[k]) for k in GEOMETRY_KEYS}
+    geometry = plan.kernel  # of the kernel that runs, as dd_plan_kernel gives it
+    runs_shared = geometry["form"] == "shared"
     traffic, traffic_note = None, "no counter record"
-    if args.tuning is None and args.traffic and os.path.exists(args.traffic):
+    if runs_shared and args.traffic and os.path.exists(args.traffic):
         from paper_1401_8258_amd.profiling import source_digest
         with open(args.traffic) as f:
             rec = json.load(f)
@@ -545,14 +545,15 @@ def main():
     roof = {"bound": "alu", "achieved": round(achieved, 3), "peak": PEAK_FP32_TFLOPS,
             "unit": "TFLOP/s", "frac": round(achieved / PEAK_FP32_TFLOPS, 4), "traffic": traffic,
             "traffic_note": traffic_note, "algorithmic_bytes": algo_bytes,
-            "kernel": "dedisp_shared" if args.tuning is None else "dedisp_tile", "kernel_ms": round(ms_kernel, 3), "geometry": geometry,
+            "kernel": "dedisp_shared" if runs_shared else "dedisp_tile", "kernel_ms": round(ms_kernel, 3),
+            "geometry": geometry,
             "achieved_note": "one FP32 add per (DM trial, channel, output sample) = one flop; the shared-sum form "
                              "forms sums that several trials have in common once, so it issues fewer",
             "peak_note": "published FP32 vector peak: 256 CU x 2.4 GHz x 128 lanes x 2 (FMA)",
             "add_issue_rate": round(PEAK_ADD_TFLOPS, 2),
             "frac_of_add_issue_rate": round(achieved / PEAK_ADD_TFLOPS, 4),
             "add_issue_rate_note": "256 CU x 2.4 GHz x 128 lanes x 1 (an add is one flop per lane)",
-            "frac_of_lds_ceiling": None if args.tuning is None else round(achieved / LDS_CEILING_TADDS, 4),
+            "frac_of_lds_ceiling": None if runs_shared else round(achieved / LDS_CEILING_TADDS, 4),
             "algorithmic_hbm_gbs": round(algo_bytes / (ms_kernel * 1e-3) / 1e9, 1)}
 
     # detrending and normalisation of the dedispersed series (Sec. 3.5, downstream of the
@@ -759,7 +760,7 @@ def main():
         e1.record(stream)
         torch.cuda.synchronize()
         u8res["step_ms" if full else "prep_and_kernel_ms"] = round(e0.elapsed_time(e1) / 3, 3)
-    u8 = {"form": plan8.form, "tiles": list(plan8.tiles[:2]), **u8res,
+    u8 = {"form": plan8.kernel["form"], "tiles": [plan8.kernel["dms_per_wave"], plan8.kernel["waves"]], **u8res,
           "adds_per_s_prep_and_kernel": adds / (u8res["prep_and_kernel_ms"] * 1e-3),
           "dm_trial_samples_per_s": beam.ndm * nout / (u8res["step_ms"] * 1e-3)}
     # RFI mitigation of the 8-bit codes in place (window 256, order 6): the bandpass and
@@ -809,7 +810,8 @@ def main():
         "config": {"workload": "plain brute-force dedispersion, full size: FP32 1024 ch 408-428 MHz, "
                                "tsamp 51.2 us, nsamp 2^20, 2048 DMs 0-204.7 step 0.1, stats + 6-sigma candidates",
                    "nchan": beam.nchan, "nsamp": nsamp, "ndm": beam.ndm, "nout": nout,
-                   "tiles": list(plan.tiles), "producer_waves": plan.producer_waves, "candidates_found": n_found},
+                   "tiles": [geometry["dms_per_wave"], geometry["waves"]],
+                   "producer_waves": geometry["producer_waves"], "candidates_found": n_found},
         "real_time_factor": round(nout * beam.tsamp_s / (ms_step * 1e-3), 2),
         "roofline": roof,
         "u8_storage": u8,

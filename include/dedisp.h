@@ -61,7 +61,8 @@ extern "C" {
                                   dd_stream_set_gap_fill;
                                4: DD_FORM_DIRECT, dd_plan_info.stream_workspace_bytes,
                                   dd_boxcar_search, dd_binned_*, dd_subband_*;
-                               5: dd_binned_stream_*, dd_bandpass_u8, dd_rfi_clip_u8 */
+                               5: dd_binned_stream_*, dd_bandpass_u8, dd_rfi_clip_u8,
+                                  dd_plan_kernel, dd_binned_kernel */
 #define DD_CHAN_BLOCK 32
 
 /* Status codes. */
@@ -112,8 +113,11 @@ enum {
      form), wherever 4
      neighbouring channels' delays allow it: sums of 4 channels that several DM trials have in
      common are formed once in LDS. dd_plan_info goes on describing the form that the plan
-     falls back to; the workspace, ring and batch calls are the same */
+     falls back to, and dd_plan_kernel the one it runs in; the workspace, ring and batch calls
+     are the same */
 };
+/* The shared-sum form in dd_kernel_info.form; not a dd_tuning.kernel_form. */
+#define DD_RUNS_SHARED 4
 
 typedef struct dd_plan dd_plan;
 typedef struct dd_stream dd_stream;
@@ -197,6 +201,21 @@ void dd_plan_destroy(dd_plan* plan);
  * DD_ERR_TOO_SHORT if nsamp <= maxdelay (info is still filled with maxdelay).
  */
 int dd_plan_query(const dd_plan* plan, int64_t nsamp, dd_plan_info* info);
+
+/*
+ * The kernel that the plan's calls run (dd_plan_query describes the tiled form that an untuned
+ * plan would otherwise take). DD_ERR_INVALID_ARG for NULL pointers.
+ */
+typedef struct dd_kernel_info {
+  int32_t form;            /* DD_FORM_LDS, DD_FORM_REGWIN, DD_FORM_DIRECT or DD_RUNS_SHARED */
+  int32_t dms_per_wave;    /* DM trials per computing wavefront */
+  int32_t waves;           /* computing wavefronts per workgroup */
+  int32_t producer_waves;  /* wavefronts that only move input */
+  int32_t dms_per_group;   /* DM trials per workgroup */
+  int32_t tile_samples;    /* output samples per workgroup */
+  int64_t lds_bytes;       /* LDS per workgroup, of the kernel's dynamic allocation */
+} dd_kernel_info;
+int dd_plan_kernel(const dd_plan* plan, dd_kernel_info* info);
 
 /* Copy the delay table, [nchan][ndm] int32 DM fastest, into host_out. */
 int dd_plan_delays(const dd_plan* plan, int32_t* host_out);
@@ -474,6 +493,8 @@ int dd_binned_create(dd_binned** out, const double* freq_mhz, int32_t nchan, dou
    would have no output (then *workspace_bytes is 0; the runs are still reported). */
 int dd_binned_query(const dd_binned* b, int64_t nsamp, int32_t* nruns, dd_binned_run* runs, int32_t runs_cap,
                     int64_t* workspace_bytes, double* dm_diag);
+/* The kernel that run `run` runs (dd_plan_kernel); DD_ERR_INVALID_ARG for no such run. */
+int dd_binned_kernel(const dd_binned* b, int32_t run, dd_kernel_info* info);
 /* Copies every run's delay table into a workspace for nsamp-sample calls. */
 int dd_binned_upload(const dd_binned* b, int64_t nsamp, void* d_workspace, int64_t ws_bytes, void* stream);
 /* One call over all runs. d_out: [ndm][out_row_stride] FP32; row d holds the nout of its

@@ -17,6 +17,7 @@ DD_ERR_HIP = -5
 DD_ERR_UNSUPPORTED = -6
 DD_F32, DD_F16, DD_U8 = 0, 1, 2
 DD_FORM_AUTO, DD_FORM_LDS, DD_FORM_REGWIN, DD_FORM_DIRECT = 0, 1, 2, 3
+DD_RUNS_SHARED = 4
 CHAN_BLOCK = 32
 
 
@@ -45,6 +46,12 @@ class PlanInfo(C.Structure):
                 ("stream_workspace_bytes", C.c_int64)]
 
 
+class KernelInfo(C.Structure):
+    _fields_ = [("form", C.c_int32), ("dms_per_wave", C.c_int32), ("waves", C.c_int32),
+                ("producer_waves", C.c_int32), ("dms_per_group", C.c_int32), ("tile_samples", C.c_int32),
+                ("lds_bytes", C.c_int64)]
+
+
 class Cand(C.Structure):
     _fields_ = [("dm_index", C.c_int32), ("reserved", C.c_int32), ("t", C.c_int64),
                 ("value", C.c_float), ("snr", C.c_float)]
@@ -68,6 +75,7 @@ SIGNATURES = {
                                  C.POINTER(Tuning)]),
     "dd_plan_destroy": (None, [_P]),
     "dd_plan_query": (C.c_int, [_P, _I64, C.POINTER(PlanInfo)]),
+    "dd_plan_kernel": (C.c_int, [_P, C.POINTER(KernelInfo)]),
     "dd_plan_delays": (C.c_int, [_P, C.POINTER(_I32)]),
     "dd_plan_upload": (C.c_int, [_P, _P, _I64, _P]),
     "dd_dedisperse": (C.c_int, [_P, _P, _I64, _I64, _P, _I64, _P, _P, _F32, _P, _I64, _P, _P, _I64, _P]),
@@ -86,6 +94,7 @@ SIGNATURES = {
                                    C.POINTER(Tuning)]),
     "dd_binned_query": (C.c_int, [_P, _I64, C.POINTER(_I32), C.POINTER(BinnedRun), _I32, C.POINTER(_I64),
                                   C.POINTER(_F64)]),
+    "dd_binned_kernel": (C.c_int, [_P, _I32, C.POINTER(KernelInfo)]),
     "dd_binned_upload": (C.c_int, [_P, _I64, _P, _I64, _P]),
     "dd_binned_dedisperse": (C.c_int, [_P, _P, _I64, _I64, _P, _I64, _P, _P, C.c_float, _P, _I64, _P, _I32, _P, _I64,
                                        _P]),

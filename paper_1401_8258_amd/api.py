@@ -31,6 +31,13 @@ _FORMS = {"auto": _lib.DD_FORM_AUTO, "lds": _lib.DD_FORM_LDS, "regwin": _lib.DD_
 _FORM_NAMES = {v: k for k, v in _FORMS.items()}
 
 
+def _kernel(info: "_lib.KernelInfo") -> dict:
+    """A dd_kernel_info as a dict, its form by name ("shared": the shared-sum form)."""
+    k = {f: int(getattr(info, f)) for f, _ in info._fields_}
+    k["form"] = "shared" if k["form"] == _lib.DD_RUNS_SHARED else _FORM_NAMES[k["form"]]
+    return k
+
+
 def _tuning(tuning, form: str):
     """The dd_tuning a (tuning tuple, form name) pair describes, by reference, or None."""
     kf = _FORMS[form]
@@ -101,7 +108,10 @@ class Result:
 
 
 class Plan:
-    """A dedispersion plan: channel frequencies (MHz), sampling time (s), DM trials, input dtype."""
+    """A dedispersion plan: channel frequencies (MHz), sampling time (s), DM trials, input dtype.
+
+    ``form`` and ``tiles`` are the tiled form's; an untuned plan may run in the shared-sum form
+    instead, which ``kernel`` tells."""
 
     def __init__(self, freq_mhz, tsamp_s: float, dm, dtype=torch.float32, tuning=None, form: str = "auto"):
         lib = _lib.load()
@@ -146,6 +156,14 @@ class Plan:
         allow = (_lib.DD_OK, _lib.DD_ERR_TOO_SHORT) if allow_short else (_lib.DD_OK,)
         check(self._lib.dd_plan_query(self._h, int(nsamp), C.byref(inf)), allow)
         return {f: getattr(inf, f) for f, _ in inf._fields_}
+
+    @property
+    def kernel(self) -> dict:
+        """The kernel the plan's calls run (dd_plan_kernel): form ("lds", "regwin", "direct" or
+        "shared"), dms_per_wave, waves, producer_waves, dms_per_group, tile_samples, lds_bytes."""
+        inf = _lib.KernelInfo()
+        check(self._lib.dd_plan_kernel(self._h, C.byref(inf)))
+        return _kernel(inf)
 
     def delays(self) -> np.ndarray:
         out = np.empty((self.nchan, self.ndm), dtype=np.int32)
@@ -582,6 +600,16 @@ class BinnedPlan(_Composite):
 
     def adds(self, nsamp: int) -> int:
         return sum((s.d1 - s.d0) * s.plan.nchan * n for s, n in zip(self.segments, self.nout(nsamp)))
+
+    @property
+    def kernels(self) -> list:
+        """Per run, the kernel it runs (Plan.kernel)."""
+        out = []
+        for i in range(len(self.segments)):
+            inf = _lib.KernelInfo()
+            check(self._lib.dd_binned_kernel(self._h, i, C.byref(inf)))
+            out.append(_kernel(inf))
+        return out
 
     @property
     def batchable(self) -> bool:

@@ -2042,6 +2042,12 @@ int dd_binned_query(const dd_binned* b, int64_t nsamp, int32_t* nruns, dd_binned
   return DD_OK;
 }
 
+int dd_binned_kernel(const dd_binned* b, int32_t run, dd_kernel_info* info) {
+  dd::clear_error();
+  if (!b || run < 0 || run >= (int32_t)b->runs.size()) return dd::fail(DD_ERR_INVALID_ARG, "no such run");
+  return dd_plan_kernel(b->runs[(size_t)run].plan, info);
+}
+
 int dd_binned_upload(const dd_binned* b, int64_t nsamp, void* d_workspace, int64_t ws_bytes, void* stream) {
   dd::clear_error();
   if (!b || !d_workspace) return dd::fail(DD_ERR_INVALID_ARG, "plan and workspace must be non-NULL");

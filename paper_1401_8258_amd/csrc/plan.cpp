@@ -910,6 +910,22 @@ int dd_plan_query(const dd_plan* p, int64_t nsamp, dd_plan_info* info) {
   return DD_OK;
 }
 
+int dd_plan_kernel(const dd_plan* p, dd_kernel_info* info) {
+  dd::clear_error();
+  if (!p || !info) return dd::fail(DD_ERR_INVALID_ARG, "plan and info must be non-NULL");
+  std::memset(info, 0, sizeof(*info));
+  info->form = p->sh.on ? DD_RUNS_SHARED : p->launch.form;
+  info->dms_per_wave = p->sh.on ? dd::kShG : p->tiles.g;
+  info->waves = p->sh.on ? p->sh.nw : p->tiles.w;
+  info->producer_waves = p->sh.on ? 0 : p->launch.prod;
+  info->dms_per_group = p->dms_per_group;
+  info->tile_samples = p->sh.on                            ? (int32_t)dd::stat_tile(p)
+                       : p->launch.form == dd::kFormDirect ? 64 * p->tiles.s
+                                                           : (int32_t)dd::kTile;
+  info->lds_bytes = p->sh.on ? p->sh.lds : p->launch.lds;
+  return DD_OK;
+}
+
 int dd_plan_delays(const dd_plan* p, int32_t* host_out) {
   dd::clear_error();
   if (!p || !host_out) return dd::fail(DD_ERR_INVALID_ARG, "plan and host_out must be non-NULL");
