@@ -108,13 +108,11 @@ enum {
                           launch per tile shape and wavefront count, beside the LDS-form
                           items' launches */
   /* Shared-sum form: no value of its own. Plans with DD_FORM_AUTO and no tile field run in it
-     (FP32 plans from 128 channels on, FP16 plans of any size; so do the steps of
-     subband plans where it is cheaper; 8-bit plans where it is cheaper than the direct-read
-     form), wherever 4
-     neighbouring channels' delays allow it: sums of 4 channels that several DM trials have in
-     common are formed once in LDS. dd_plan_info goes on describing the form that the plan
-     falls back to, and dd_plan_kernel the one it runs in; the workspace, ring and batch calls
-     are the same */
+     where it is estimated to be the cheaper form (FP32 plans from 128 channels on, FP16 and
+     8-bit plans of any size, the steps of subband plans): sums of up to 4 neighbouring
+     channels that several DM trials have in common are formed once in LDS. dd_plan_info goes on
+     describing the form that the plan falls back to, and dd_plan_kernel the one it runs in; the
+     workspace, ring and batch calls are the same */
 };
 /* The shared-sum form in dd_kernel_info.form; not a dd_tuning.kernel_form. */
 #define DD_RUNS_SHARED 4

@@ -97,9 +97,23 @@ constexpr double kShFewClk = 160.0;
 // trials at low frequencies leave one channel a bundle and long windows: at 290 to 410 clocks
 // (512 to 4096 channels of 120-180 MHz, steps of 0.2 and 0.25) the shared-sum form took 1.25 to
 // 1.6 times the direct-read form's time, at 170 to 190 1.02 to 1.09 times, at 115 0.81, at 92
-// (4096 channels, steps of 0.05) 0.5 and at 49 (408-428 MHz) 0.26. FP32 and FP16 need no such
-// rule: the LDS form loses as much there (never faster on the same beams, 1.4 to 14 times slower).
+// (4096 channels, steps of 0.05) 0.5 and at 49 (408-428 MHz) 0.26.
 constexpr double kShDirectClk = 140.0;
+// An FP32 plan of more than kShLdsTrials trials whose LDS form keeps its best tiling (14 wavefronts
+// of 4 trials: windows of up to 1024 words) takes that form where the shared-sum form's estimated
+// clocks per trial (with both forms' padding) and 4 channels are kShLdsClk or more: the LDS form
+// does not care which channels neighbour each other. 256 and 1024 channels of 408-428 MHz, 500 and
+// 1000 trials, 65,536 to 262,144 samples: the shared-sum form takes 1.07 to 1.5 times the LDS form's
+// time at 147 to 155 clocks (channels in no order), 0.96 to 1.28 times at 121 to 126 (three in four
+// shuffled), 0.81 to 1.12 at 105 (threes), 0.76 to 1.01 at 95 (half shuffled), 0.69 to 0.94 at 84
+// (pairs). With fewer trials the LDS form leaves the chip idle on all but long inputs: at 350 trials
+// in no order the shared-sum form takes 0.96 to 1.03 times its time on 65,536 samples (1.35 on
+// 262,144), at 100 and 200 trials 0.33 to 0.72 on 16,384 and 65,536 (1.0 to 1.2 on 262,144). Where
+// longer delays leave it fewer wavefronts it loses at any cost (steps of 0.3 and 0.5 in no order:
+// 1.16 to 1.8 times slower; coarser ordered beams 4 to 70 times), and for FP16 input, which it
+// takes without producers, everywhere (1.1 times slower at least).
+constexpr double kShLdsClk = 112.0;
+constexpr int kShLdsTrials = 384;
 constexpr int kShMaxBundles = 3;  // bundles of a stage
 constexpr int kShBlock = 136;     // bytes of code per pattern block
 constexpr int kShSpare = 1024;    // LDS bytes before the stages: where lanes without a chunk write

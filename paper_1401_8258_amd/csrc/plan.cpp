@@ -530,8 +530,11 @@ bool plan_shared(dd_plan* p, int64_t lds_cap, double max_cost) {
   const int nw = maxw / best_div, n = G * nw;
   const int64_t cap = (lds_cap / best_div - kShSpare) / 2 / 256 * 256;
   const int ng = (ndm + n - 1) / n;
-  // ndm_pad is still the direct-read form's (kShDirectClk)
-  if (p->dtype == DD_U8 && !(best * ((double)ng * n) < kShDirectClk * p->ndm_pad)) return false;
+  // ndm_pad is still the other form's (kShDirectClk, kShLdsClk)
+  const double clk = best * ((double)ng * n) / p->ndm_pad;
+  if (p->dtype == DD_U8 && !(clk < kShDirectClk)) return false;
+  const bool lds_best = p->dtype == DD_F32 && p->tiles.g == 4 && p->tiles.w == 14 && ndm > kShLdsTrials;
+  if (lds_best && !(clk < kShLdsClk)) return false;
   const int ints = sh_stage_ints(nw);
   std::vector<int32_t> tab((size_t)(2 * ng + 63) / 64 * 64 + (size_t)ints, 0);
   int64_t max_reach = 0;
@@ -720,8 +723,8 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
     t.cc = tuning->chan_stage;
     t.pw = tuning->producer_waves;
   }
-  // a plan without any choice of the caller's runs in the shared-sum form, except FP32 beams of
-  // few channels (kShMinChans)
+  // a plan without any choice of the caller's runs in the shared-sum form where it pays
+  // (plan_shared), except FP32 beams of few channels (kShMinChans)
   const bool auto_form =
       form_req == DD_FORM_AUTO && !tiles_set && (shared_any || !(in_dtype == DD_F32 && nchan < dd::kShMinChans));
   const double sh_cost = in_dtype == DD_F32 && nchan < dd::kShMinChans ? dd::kShFewClk

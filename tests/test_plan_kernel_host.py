@@ -82,3 +82,35 @@ def test_binned_kernel_and_errors(lib):
     assert lib.dd_plan_kernel(None, C.byref(k)) == _lib.DD_ERR_INVALID_ARG
     # the shared-sum form is no tuning
     assert _plan(lib, f, dm, ts, F32, (0, 0, 0, 0, 0, SHARED))[0] == _lib.DD_ERR_UNSUPPORTED
+
+
+def _order(freq, how):
+    rng = np.random.default_rng(3)
+    if how == "none":
+        return rng.permutation(freq)
+    if how == "halves":  # two halves of the band, channel by channel
+        return np.stack([freq[: freq.size // 2], freq[freq.size // 2:]], 1).ravel()
+    if how == "pairs":
+        return freq.reshape(-1, 2)[rng.permutation(freq.size // 2)].ravel()
+    return freq
+
+
+@pytest.mark.parametrize("order,ndm,step,dtype,runs", [
+    ("down", 500, 0.1, F32, SHARED),
+    ("pairs", 500, 0.1, F32, SHARED),
+    ("none", 500, 0.1, F32, LDS),      # neighbours share no sums: the LDS form takes two thirds of the time
+    ("halves", 500, 0.1, F32, LDS),
+    ("none", 2048, 0.1, F32, LDS),
+    ("none", 350, 0.1, F32, SHARED),   # too few trials to fill the chip in the LDS form
+    ("none", 500, 0.5, F32, SHARED),   # long windows: no 14-wavefront tiling
+    ("none", 500, 0.1, F16, SHARED),   # the LDS form has no producers
+    ("none", 500, 0.1, U8, DIRECT),
+])
+def test_beams_whose_channels_share_nothing(lib, order, ndm, step, dtype, runs):
+    freq, ts = _mid(1024)
+    rc, h = _plan(lib, _order(freq, order), fbsynth.dm_trials(0.0, step, ndm), ts, dtype)
+    assert rc == 0, lib.dd_last_error()
+    k = _lib.KernelInfo()
+    assert lib.dd_plan_kernel(h, C.byref(k)) == 0
+    assert k.form == runs
+    lib.dd_plan_destroy(h)
