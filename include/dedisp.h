@@ -313,17 +313,17 @@ int dd_stream_set_gap_fill(dd_stream* s, int32_t enable);
 int dd_candidates_check(const int64_t* d_ncand, int64_t cand_cap, void* stream, int64_t* ncand_out);
 
 /*
- * Batched launch (uneven beams in few persistent launches). Each item names a plan, an
+ * Batched launch (uneven beams in few launches). Each item names a plan, an
  * input already resident on the device, and its outputs; or a stream whose block has
  * already been appended with dd_stream_append. Items on the same kernel and workgroup shape
  * (LDS form: input dtype, computing and producer wavefronts, DM trials per wavefront;
- * direct-read form: DM trials per wavefront, samples per lane, wavefronts) run in one
- * launch that walks a device queue of (item, DM group, time tile) work, one launch per
- * distinct shape, each item on its own plan's tiles (an item of many units takes its plain
- * launch instead, as does an item in the shared-sum form, whose one launch fills the chip by
- * its own work units); then the statistics and candidates of all items take one launch per
- * step. The results equal those of one dd_dedisperse per
- * item, bit for bit. Register-window plans are refused (DD_ERR_UNSUPPORTED).
+ * direct-read form: DM trials per wavefront, samples per lane, wavefronts; shared-sum form:
+ * input dtype and wavefronts) run in one launch that walks a device queue of (item, DM group,
+ * time tile) work, one launch per distinct shape, each item on its own plan's tiles (an item
+ * of many units in one of the first two forms takes its plain launch instead); then the
+ * statistics and candidates of all items take one launch per step. The results equal those of
+ * one dd_dedisperse per item, bit for bit. Register-window plans are refused
+ * (DD_ERR_UNSUPPORTED).
  */
 typedef struct dd_batch_item {
   const dd_plan* plan;
@@ -580,10 +580,10 @@ int dd_subband_query(const dd_subband* sp, int64_t nsamp, int64_t* workspace_byt
                      int64_t* adds, int32_t* nsub, int32_t* ngroups);
 int dd_subband_upload(const dd_subband* sp, int64_t nsamp, void* d_workspace, int64_t ws_bytes, void* stream);
 /* One call over both steps; outputs and candidates as dd_binned_dedisperse (row d holds
-   its group's nout; times in input samples). batched != 0 runs a step without plans in the
-   shared-sum form through one dd_batch_dedisperse call (same results bit for bit). Otherwise
-   the plans of each step run on four side streams of the calling host thread (as
-   dd_binned_dedisperse's) and `stream` waits for them. */
+   its group's nout; times in input samples). batched != 0 runs each step through one
+   dd_batch_dedisperse call (same results bit for bit). Unbatched, the plans of each step run
+   on four side streams of the calling host thread (as dd_binned_dedisperse's) and `stream`
+   waits for them. */
 int dd_subband_dedisperse(const dd_subband* sp, const float* d_in, int64_t nsamp, int64_t in_row_stride, float* d_out,
                           int64_t out_row_stride, float* d_mean, float* d_rms, float k_sigma, dd_cand* d_cand,
                           int64_t cand_cap, int64_t* d_ncand, int32_t batched, void* d_workspace, int64_t ws_bytes,

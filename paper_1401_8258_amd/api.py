@@ -325,12 +325,12 @@ def alloc_outputs(ndm: int, ncols: int, device, k_sigma: float = 0.0, cand_cap: 
 
 def batch_dedisperse(jobs, k_sigma: float = 0.0, cand_cap: int = 1 << 16, stats: bool = True, stream=None,
                      outputs=None):
-    """Dedisperse several inputs in one batched call (dd_batch_dedisperse): one persistent
-    launch per kernel shape.
+    """Dedisperse several inputs in one batched call (dd_batch_dedisperse): one launch per
+    kernel shape over all its jobs' work.
 
     jobs: a list of (Plan, tensor) pairs and/or (Stream, (t0, nout)) pairs, the latter
     after Stream.append returned a pending window. Plans of any tiles and forms mix, except
-    the register-window form; the jobs on one kernel and workgroup shape share a persistent
+    the register-window form; the jobs on one kernel and workgroup shape share a
     launch, each on its own tiles. Statistics and candidates of all jobs run in one launch
     per step. ``outputs`` optionally gives, per job, buffers from
     alloc_outputs (with ``stats`` and ``k_sigma`` matching) to write into instead of new

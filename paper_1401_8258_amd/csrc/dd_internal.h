@@ -145,6 +145,7 @@ struct Shared {
   int32_t nw = 0;      // wavefronts per workgroup
   int32_t mirror = 0;  // samples past a window's start that a unit may read
   int64_t lds = 0;     // bytes (the spare slot and two stages)
+  double stages = 0;   // per group, on average
 };
 
 struct Tiles {
@@ -261,6 +262,20 @@ int launch_regwin(const dd_plan* p, const InView& in, const int32_t* d_table, in
 bool plan_shared(dd_plan* p, int64_t lds_cap, double max_cost);
 int launch_shared(const dd_plan* p, const InView& in, const int32_t* d_table, int64_t nout, float* out,
                   int64_t out_stride, double* part, void* stream);
+// One shared-sum item of a batched call; the items of one input type and workgroup size run in
+// one launch over all their units.
+struct SharedItem {
+  const dd_plan* plan;
+  InView in;
+  const int32_t* table;
+  int64_t nout;
+  float* out;
+  int64_t out_stride;
+  double* part;
+};
+// Bytes of device descriptors a batched shared-sum launch of n items uploads.
+int64_t shared_batch_desc_bytes(int32_t n);
+int launch_shared_batch(const std::vector<SharedItem>& items, void* d_desc, int64_t desc_bytes, void* stream);
 // Direct-read form (8-bit input): device table [nchan][ndm_pad] of plain delays (padded trials
 // repeat the last DM). Fills the plan's tiles, groups, launch and table.
 int plan_direct(dd_plan* p, const Tiles& t);

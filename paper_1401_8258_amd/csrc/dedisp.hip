@@ -1583,9 +1583,9 @@ int dd_batch_query(const dd_batch_item* items, int32_t n, int64_t* ws_bytes) {
   if (!ws_bytes || n < 1 || !items) return dd::fail(DD_ERR_INVALID_ARG, "need items, n >= 1 and ws_bytes");
   // descriptors of the LDS-form launches (the records, then per launch the XCD runs
   // [8][items + 1]: at most 8 * 2n entries over at most n launches), then of the direct-read
-  // launches
+  // launches, then of the shared-sum launches
   *ws_bytes = dd::align_up((int64_t)n * (int64_t)sizeof(KParams)) + dd::align_up((int64_t)8 * 8 * 2 * n) +
-              dd::direct_batch_desc_bytes(n) + 2 * dd::align_up((int64_t)n * (int64_t)sizeof(TailItem));
+              dd::direct_batch_desc_bytes(n) + dd::shared_batch_desc_bytes(n) + 2 * dd::align_up((int64_t)n * (int64_t)sizeof(TailItem));
   return DD_OK;
 }
 
@@ -1611,9 +1611,7 @@ int dd_batch_dedisperse(const dd_batch_item* items, int32_t n, void* d_workspace
   std::vector<Outputs> outs((size_t)n);
   std::vector<int64_t> nouts((size_t)n);
   std::vector<dd::WsLayout> lays((size_t)n);
-  std::vector<int32_t> shared;  // shared-sum items
-  std::vector<InView> views((size_t)n);
-  std::vector<const int32_t*> tables((size_t)n);
+  std::vector<dd::SharedItem> shared;  // shared-sum items
   for (int32_t i = 0; i < n; ++i) {
     const dd_batch_item& it = items[i];
     dd_stream* sp = it.stream_item;
@@ -1663,14 +1661,12 @@ int dd_batch_dedisperse(const dd_batch_item* items, int32_t n, void* d_workspace
     outs[i] = Outputs{it.d_out, it.out_row_stride, it.d_mean, it.d_rms, it.k_sigma, it.d_cand, it.cand_cap,
                       it.d_ncand, t_base};
     nouts[i] = nout;
+    double* part = (it.d_mean && it.d_rms) ? reinterpret_cast<double*>(ws + lays[i].part_off) : nullptr;
     if (p->sh.on) {
-      shared.push_back(i);
-      views[i] = in;
-      tables[i] = table;
+      shared.push_back(dd::SharedItem{p, in, table, nout, it.d_out, it.out_row_stride, part});
       continue;
     }
     if (is_direct) {
-      double* part = (it.d_mean && it.d_rms) ? reinterpret_cast<double*>(ws + lays[i].part_off) : nullptr;
       direct.push_back(dd::DirectItem{p, in, table, nout, it.d_out, it.out_row_stride, part, ws + lays[i].quad_off});
       continue;
     }
@@ -1776,14 +1772,9 @@ int dd_batch_dedisperse(const dd_batch_item* items, int32_t n, void* d_workspace
   const int64_t direct_desc = dd::direct_batch_desc_bytes(n);
   rc = dd::launch_direct_batch(direct, bw + lds_desc, direct_desc, st);
   if (rc) return rc;
-  for (int32_t i : shared) {
-    const dd_batch_item& it = items[i];
-    const dd_plan* p = it.stream_item ? it.stream_item->plan : it.plan;
-    char* ws = static_cast<char*>(it.d_plan_workspace);
-    double* part = (it.d_mean && it.d_rms) ? reinterpret_cast<double*>(ws + lays[i].part_off) : nullptr;
-    rc = dd::launch_shared(p, views[i], tables[i], nouts[i], it.d_out, it.out_row_stride, part, st);
-    if (rc) return rc;
-  }
+  const int64_t shared_desc = dd::shared_batch_desc_bytes(n);
+  rc = dd::launch_shared_batch(shared, bw + lds_desc + direct_desc, shared_desc, st);
+  if (rc) return rc;
   // statistics and candidates of every item: one launch per step for the whole batch
   std::vector<TailItem> tails, cands;
   int64_t nser = 0, nunit = 0;
@@ -1823,8 +1814,8 @@ int dd_batch_dedisperse(const dd_batch_item* items, int32_t n, void* d_workspace
   }
   if (!tails.empty()) {
     const int64_t tail_bytes = dd::align_up((int64_t)n * (int64_t)sizeof(TailItem));
-    TailItem* dT = reinterpret_cast<TailItem*>(bw + lds_desc + direct_desc);
-    TailItem* dC = reinterpret_cast<TailItem*>(bw + lds_desc + direct_desc + tail_bytes);
+    TailItem* dT = reinterpret_cast<TailItem*>(bw + lds_desc + direct_desc + shared_desc);
+    TailItem* dC = reinterpret_cast<TailItem*>(bw + lds_desc + direct_desc + shared_desc + tail_bytes);
     hipError_t e = hipMemcpyAsync(dT, tails.data(), tails.size() * sizeof(TailItem), hipMemcpyHostToDevice, st);
     if (e == hipSuccess && !cands.empty())
       e = hipMemcpyAsync(dC, cands.data(), cands.size() * sizeof(TailItem), hipMemcpyHostToDevice, st);
@@ -2696,14 +2687,8 @@ int dd_subband_dedisperse(const dd_subband* sp, const float* d_in, int64_t nsamp
     if (r) return r;
     return e != hipSuccess ? hip_fail(e, what) : DD_OK;
   };
-  // a batched call takes a launch for each plan in the shared-sum form, so a step with such plans
-  // goes over the side streams there too (1024 channels x 2^19 samples x 960 trials: 5.8 ms, 7.1
-  // with the launches on one stream)
-  auto one_launch = [&](const std::vector<dd_plan*>& plans) {
-    return batched && !std::any_of(plans.begin(), plans.end(), [](const dd_plan* p) { return p->sh.on; });
-  };
   // step 1: subband s at the nominal DMs into red[s][g][:]
-  if (one_launch(sp->step1)) {
+  if (batched) {
     std::vector<dd_batch_item> items(sp->step1.size());
     for (size_t s = 0; s < sp->step1.size(); ++s) {
       dd_batch_item& it = items[s];
@@ -2733,7 +2718,7 @@ int dd_subband_dedisperse(const dd_subband* sp, const float* d_in, int64_t nsamp
     if (rc) return rc;
   }
   // step 2: group g over the reduced filterbank red[:][g][0 .. len1)
-  if (one_launch(sp->step2)) {
+  if (batched) {
     std::vector<dd_batch_item> items(sp->step2.size());
     for (size_t g = 0; g < sp->step2.size(); ++g) {
       dd_batch_item& it = items[g];

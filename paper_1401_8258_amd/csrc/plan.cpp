@@ -537,7 +537,7 @@ bool plan_shared(dd_plan* p, int64_t lds_cap, double max_cost) {
   if (lds_best && !(clk < kShLdsClk)) return false;
   const int ints = sh_stage_ints(nw);
   std::vector<int32_t> tab((size_t)(2 * ng + 63) / 64 * 64 + (size_t)ints, 0);
-  int64_t max_reach = 0;
+  int64_t max_reach = 0, stages = 0;
   std::vector<int> order;
   // a group's records of further rounds, after its stages: (the record to link from, their place)
   std::vector<int32_t> over;
@@ -649,6 +649,7 @@ bool plan_shared(dd_plan* p, int64_t lds_cap, double max_cost) {
     tab.insert(tab.end(), over.begin(), over.end());
     tab[2 * (size_t)g] = (int32_t)first;
     tab[2 * (size_t)g + 1] = nst;
+    stages += nst;
     if (tab.size() > ((size_t)1 << 29)) return false;
     if (g == 0) tab.reserve(std::min((size_t)1 << 29, tab.size() * (size_t)ng / 4 * 5));
   }
@@ -656,6 +657,7 @@ bool plan_shared(dd_plan* p, int64_t lds_cap, double max_cost) {
   p->sh.nw = nw;
   p->sh.lds = kShSpare + 2 * cap;
   p->sh.mirror = (int32_t)max_reach;
+  p->sh.stages = (double)stages / ng;
   p->dms_per_group = n;
   p->ngroups = ng;
   p->ndm_pad = ng * n;

@@ -280,7 +280,7 @@ class Server:
 class LibraryExecutor(Executor):
     """Device side on libdedisp: one Stream (device ring with the maxdelay overlap) per
     admitted beam, and per submitted set of blocks one batched call over all of them (one
-    persistent launch per kernel shape, each beam on its own tiles).
+    launch per kernel shape, each beam on its own tiles).
     A beam with time binning (``max_log2 > 0``) has a BinnedStream instead, one ring per run
     at its binned sampling time, and is pushed on its own after the batched calls.
 
