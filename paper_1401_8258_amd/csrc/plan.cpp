@@ -5,6 +5,7 @@
 #include <cmath>
 #include <cstring>
 #include <limits>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -677,10 +678,20 @@ const char* dd_version(void) { return "1.5"; }
 
 namespace dd {
 
-// dd_plan_create with the LDS bytes one workgroup may take (the ring and slots are sized
-// within it; a smaller budget lets several workgroups share a CU).
-int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsamp_s, const double* dm,
-                int32_t ndm, int32_t in_dtype, const dd_tuning* tuning, int64_t lds_cap, bool shared_any) {
+namespace {
+
+// plan_shared, or no shared-sum form where its table, which may be several times the others', does
+// not fit the host's memory.
+bool try_shared(dd_plan* p, int64_t lds_cap, double max_cost) {
+  try {
+    return plan_shared(p, lds_cap, max_cost);
+  } catch (const std::bad_alloc&) {
+    return false;
+  }
+}
+
+int create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsamp_s, const double* dm,
+           int32_t ndm, int32_t in_dtype, const dd_tuning* tuning, int64_t lds_cap, bool shared_any) {
   dd::clear_error();
   if (!out) return dd::fail(DD_ERR_INVALID_ARG, "out is NULL");
   *out = nullptr;
@@ -746,8 +757,8 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
   if (!direct && t.g == 4 && (in_dtype != DD_F32 || t.pw < 0))
     return dd::fail(DD_ERR_UNSUPPORTED, "4 DM trials per wavefront is the FP32 producer form only");
 
-  dd_plan* p = new (std::nothrow) dd_plan();
-  if (!p) return dd::fail(DD_ERR_INVALID_ARG, "out of host memory");
+  std::unique_ptr<dd_plan> owner(new dd_plan());
+  dd_plan* p = owner.get();
   p->nchan = nchan;
   p->ndm = ndm;
   p->dtype = in_dtype;
@@ -763,10 +774,8 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
   int32_t maxd = 0;
   for (int32_t c = 0; c < nchan; ++c) {
     const double diff = 1.0 / (freq_mhz[c] * freq_mhz[c]) - inv_ref;
-    if (!(((kDm * dm[ndm - 1]) * diff) / tsamp_s < (double)std::numeric_limits<int32_t>::max() + 0.5)) {
-      delete p;
+    if (!(((kDm * dm[ndm - 1]) * diff) / tsamp_s < (double)std::numeric_limits<int32_t>::max() + 0.5))
       return dd::fail(DD_ERR_INVALID_ARG, "delay exceeds 2^31-1 samples");
-    }
     int32_t* row = &p->delays[(size_t)c * ndm];
     for (int32_t d = 0; d < ndm; ++d) {
       const double x = ((kDm * dm[d]) * diff) / tsamp_s;
@@ -779,26 +788,21 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
 
   if (direct) {
     const int rc = dd::plan_direct(p, t);
-    if (rc) {
-      delete p;
-      return rc;
-    }
-    if (!(auto_form && dd::plan_shared(p, lds_cap, sh_cost))) dd::table_direct(p);
+    if (rc) return rc;
+    if (!(auto_form && try_shared(p, lds_cap, sh_cost))) dd::table_direct(p);
     p->id = g_next_id.fetch_add(1);
-    *out = p;
+    *out = owner.release();
     return DD_OK;
   }
   if (try_regwin) {
     if (dd::plan_regwin(p, lds_cap)) {
       p->id = g_next_id.fetch_add(1);
-      *out = p;
+      *out = owner.release();
       return DD_OK;
     }
-    if (form_req == DD_FORM_REGWIN) {
-      delete p;
+    if (form_req == DD_FORM_REGWIN)
       return dd::fail(DD_ERR_UNSUPPORTED, "the delay spread of 8 consecutive DM trials does not fit the register "
                                           "window (at most 40 samples with the alignment)");
-    }
   }
   // FP32 input: by default two producer wavefronts issue every LDS DMA beside the computing
   // ones, when one DM group's channel windows fit their 16-byte DMAs. Otherwise, and for
@@ -830,11 +834,9 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
     }
   }
   if (in_dtype == DD_F32 && !placed) {
-    if (t.pw > 0 || t.g == 4) {
-      delete p;
+    if (t.pw > 0 || t.g == 4)
       return dd::fail(DD_ERR_UNSUPPORTED, "one DM group's windows do not fit the producer wavefronts' "
                                           "16-byte DMAs; use fewer DMs per workgroup or no producer");
-    }
     if (!(tuning && tuning->waves)) t.w = 0;  // automatic: fall back to the other form
   }
   const int w_opts[4] = {8, 4, 2, 1};
@@ -847,11 +849,9 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
       break;
     }
   }
-  if (lg.nb < 2) {
-    delete p;
+  if (lg.nb < 2)
     return dd::fail(DD_ERR_UNSUPPORTED, "delay spread of one DM group (" + std::to_string(span) +
                                             " samples) does not fit in LDS; use fewer DMs per workgroup");
-  }
   p->tiles = t;
   lg.form = dd::kFormLds;
   p->launch = lg;
@@ -859,10 +859,23 @@ int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsa
   p->ngroups = (ndm + p->dms_per_group - 1) / p->dms_per_group;
   p->ndm_pad = p->ngroups * p->dms_per_group;
   p->max_span = span;
-  if (!(auto_form && dd::plan_shared(p, lds_cap, sh_cost))) dd::table_lds(p);
+  if (!(auto_form && try_shared(p, lds_cap, sh_cost))) dd::table_lds(p);
   p->id = g_next_id.fetch_add(1);
-  *out = p;
+  *out = owner.release();
   return DD_OK;
+}
+
+}  // namespace
+
+// dd_plan_create with the LDS bytes one workgroup may take (the ring and slots are sized
+// within it; a smaller budget lets several workgroups share a CU).
+int plan_create(dd_plan** out, const double* freq_mhz, int32_t nchan, double tsamp_s, const double* dm,
+                int32_t ndm, int32_t in_dtype, const dd_tuning* tuning, int64_t lds_cap, bool shared_any) {
+  try {
+    return create(out, freq_mhz, nchan, tsamp_s, dm, ndm, in_dtype, tuning, lds_cap, shared_any);
+  } catch (const std::bad_alloc&) {
+    return fail(DD_ERR_INVALID_ARG, "out of host memory");
+  }
 }
 
 }  // namespace dd
