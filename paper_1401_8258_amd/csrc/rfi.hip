@@ -224,10 +224,25 @@ __global__ __launch_bounds__(kRfiThreads) void chan_correct(float* __restrict__ 
 // fitted value, giving back the uncorrected spectrum to compare, and a replaced spectrum
 // becomes 0. A pass reads the block once, and what bounds it is how many reads are under way:
 // a lane's sum is one chain over the channels, so the loads of kClipAhead channels are issued
-// before their additions. One sample a lane and not four (16-byte loads) gives four times the
-// wavefronts for the same block and needs no alignment: 1024 channels x 262,144 samples took
-// 0.524 ms with four samples a lane and the loads one by one, 0.249 ms now (floor 0.2 ms).
+// before their additions, those of the last ones 8, 4 and 2 together. One sample a lane and not
+// four (16-byte loads) gives four times the wavefronts for the same block and needs no alignment:
+// 1024 channels x 262,144 samples took 0.524 ms with four samples a lane and the loads one by one,
+// 0.249 ms now (floor 0.2 ms); 16 channels x 4,194,304 samples take 38 us either way, 88 with the
+// last channels' loads one by one.
 constexpr int kClipAhead = 32;
+// Adds channels c .. c + N - 1 of a column to s, their loads issued together.
+template <int N>
+__device__ __forceinline__ void add_channels(const float* col, int64_t stride, const double* fit, int subtract,
+                                             int64_t& c, int64_t nchan, double& s) {
+  for (; c + N <= nchan; c += N) {
+    float v[N];
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = col[(c + k) * stride];
+#pragma unroll
+    for (int k = 0; k < N; ++k) s += (double)v[k] + (subtract ? (double)(float)fit[c + k] : 0.0);
+  }
+}
+
 __global__ __launch_bounds__(kClipThreads) void spec_clip(float* __restrict__ x, int64_t nchan, int64_t n,
                                                           int64_t stride, const double* __restrict__ fit,
                                                           double center, double thr, int subtract) {
@@ -235,14 +250,11 @@ __global__ __launch_bounds__(kClipThreads) void spec_clip(float* __restrict__ x,
     float* const col = x + t;
     double s = 0.0;
     int64_t c = 0;
-    for (; c + kClipAhead <= nchan; c += kClipAhead) {
-      float v[kClipAhead];
-#pragma unroll
-      for (int k = 0; k < kClipAhead; ++k) v[k] = col[(c + k) * stride];
-#pragma unroll
-      for (int k = 0; k < kClipAhead; ++k) s += (double)v[k] + (subtract ? (double)(float)fit[c + k] : 0.0);
-    }
-    for (; c < nchan; ++c) s += (double)col[c * stride] + (subtract ? (double)(float)fit[c] : 0.0);
+    add_channels<kClipAhead>(col, stride, fit, subtract, c, nchan, s);
+    add_channels<8>(col, stride, fit, subtract, c, nchan, s);
+    add_channels<4>(col, stride, fit, subtract, c, nchan, s);
+    add_channels<2>(col, stride, fit, subtract, c, nchan, s);
+    add_channels<1>(col, stride, fit, subtract, c, nchan, s);
     if (fabs(s / (double)nchan - center) > thr)
       for (c = 0; c < nchan; ++c) col[c * stride] = subtract ? 0.f : (float)fit[c];
   }
@@ -548,8 +560,10 @@ extern "C" int dd_rfi_clip(float* d_data, int64_t nchan, int64_t nsamp, int64_t 
   }
   if (spec_threshold > 0.0) {
     if (nsamp > INT64_C(0x7fffffff) * 4 * kRfiThreads) return dd::fail(DD_ERR_UNSUPPORTED, "series too long");
-    // a grid holds fewer than 2^32 threads; longer series go round the kernel's loop
-    const int64_t tblocks = std::min<int64_t>((nsamp + kClipThreads - 1) / kClipThreads, 1 << 24);
+    // a grid holds fewer than 2^32 threads, and with few channels a workgroup is over before the
+    // next ones are dispatched: longer series go round the kernel's loop
+    const int64_t most = nchan < kClipAhead ? 1 << 14 : 1 << 24;
+    const int64_t tblocks = std::min<int64_t>((nsamp + kClipThreads - 1) / kClipThreads, most);
     hipLaunchKernelGGL(spec_clip, dim3((unsigned)tblocks), dim3(kClipThreads), 0, st, d_data, nchan, nsamp, row_stride,
                        d_fit, fit_mean, spec_threshold, (int)sub);
     if (launched("spectrum clip") != hipSuccess) return DD_ERR_HIP;
