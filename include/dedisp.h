@@ -255,7 +255,9 @@ int dd_dedisperse(const dd_plan* plan, const void* d_in, int64_t nsamp, int64_t 
  * process ends; every call on a device shares it, so calls that overlap on one device
  * (on one stream or several) race and must not be issued. Nothing in the array needs to
  * start at zero. DD_ERR_UNSUPPORTED when the shape needs more scratch than the array holds
- * (the full 1024-channel, 2^20-sample, 2048-trial FP32 workload needs 67 MiB).
+ * (the full 1024-channel, 2^20-sample, 2048-trial FP32 workload needs 67 MiB); 8-bit plans are
+ * held to what the direct-read form needs, the four copies of their input included, whichever
+ * form they run in.
  */
 int dd_dedisperse_noalloc(const dd_plan* plan, const void* d_in, int64_t nsamp, int64_t in_row_stride,
                           float* d_out, int64_t out_row_stride, float* d_mean, float* d_rms, float k_sigma,

@@ -1381,9 +1381,12 @@ int dd_dedisperse_noalloc(const dd_plan* p, const void* d_in, int64_t nsamp, int
   const int64_t copies =
       p->sh.on && p->launch.form == dd::kFormDirect ? 4 * (int64_t)p->nchan * dd::direct_quad_row(nsamp) : 0;
   if (l.total - base + copies > kScratchBytes)
-    return dd::fail(DD_ERR_UNSUPPORTED, "this call needs " + std::to_string(l.total - base + copies) +
-                                            " bytes of scratch; the static scratch holds " +
-                                            std::to_string(kScratchBytes));
+    return dd::fail(DD_ERR_UNSUPPORTED,
+                    "this call needs " + std::to_string(l.total - base) + " bytes of scratch" +
+                        (copies ? ", " + std::to_string(l.total - base + copies) +
+                                      " with the input copies of the direct-read form, which 8-bit plans must leave room for"
+                                : "") +
+                        "; the static scratch holds " + std::to_string(kScratchBytes));
   l.part_off -= base;
   l.thr_off -= base;
   l.cnt_off -= base;
