@@ -267,9 +267,10 @@ int dd_dedisperse_noalloc(const dd_plan* plan, const void* d_in, int64_t nsamp, 
  * Streaming (Ch. 3 Sec. "Dedispersion": the last maxshift spectra of a buffer are
  * carried into the next). A stream keeps a per-channel device ring of the last
  * maxdelay + block_nsamp samples (rounded up to 64), each row followed by a mirror of
- * its first launch_buf + 64 samples so that no channel window wraps, in the caller's
- * d_ring (ring_bytes >= dd_plan_query(plan, block_nsamp).ring_bytes). The ring also
- * holds the delay table, uploaded at creation on the given stream.
+ * its first samples (launch_buf + 64 of them, or as many as a window of the shared-sum form
+ * reads) so that no channel window wraps, in the caller's d_ring (ring_bytes >=
+ * dd_plan_query(plan, block_nsamp).ring_bytes). The ring also holds the delay table, uploaded
+ * at creation on the given stream.
  */
 int dd_stream_create(const dd_plan* plan, int64_t block_nsamp, void* d_ring, int64_t ring_bytes,
                      void* stream, dd_stream** out);

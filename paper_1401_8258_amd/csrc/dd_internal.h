@@ -82,9 +82,9 @@ constexpr int kShMaxE = 3;        // largest shift of a channel in a pattern
 // (bundles of mostly two, one and four channels; always 128 channels: 1.33 / 1.66 / 0.84 and 1.98 /
 // 2.34 / 0.68).
 constexpr int kShFold = 128;
-// FP32 plans of fewer channels keep the LDS form: their few, wide channels share little (8 to
-// 14 patterns per 16 to 32 trials at 64 channels, 4 at 1024), and their series stay those of
-// every explicit tiling, bit for bit.
+// FP32 plans of fewer channels keep the LDS form, so that their series stay those of every explicit
+// tiling, bit for bit: that is what this line is for. Their few, wide channels share less (8 to 14
+// patterns per 16 to 32 trials at 64 channels, 4 at 1024), but enough to gain (kShFewClk).
 constexpr int kShMinChans = 128;
 // The steps of a subband plan (few channels: neighbouring pairs share sums, hardly fours) take the
 // shared-sum form where its clocks per trial and 4 channels, estimated, are below this. Up to
@@ -94,10 +94,13 @@ constexpr int kShMinChans = 128;
 constexpr double kShFewClk = 160.0;
 // An 8-bit plan takes the shared-sum form where its estimated clocks per trial (with both forms'
 // padding) and 4 channels are below this, else the direct-read form. Wide channels and coarse
-// trials at low frequencies leave one channel a bundle and long windows: at 290 to 410 clocks
-// (512 to 4096 channels of 120-180 MHz, steps of 0.2 and 0.25) the shared-sum form took 1.25 to
-// 1.6 times the direct-read form's time, at 170 to 190 1.02 to 1.09 times, at 115 0.81, at 92
-// (4096 channels, steps of 0.05) 0.5 and at 49 (408-428 MHz) 0.26.
+// trials at low frequencies leave one channel a bundle and long windows: at 207 to 340 clocks
+// (512 to 4096 channels of 120-180 MHz, steps of 0.1 to 0.2) the shared-sum form took 1.16 to 2.1
+// times the direct-read form's time, at 193 1.26, at 91 (4096 channels, steps of 0.05) 0.46 to 0.51
+// and at 49 (408-428 MHz) 0.26. In between the clocks do not tell the two apart, as the direct-read
+// form's time varies too: at 131 to 135 0.71 (130 channels x 200 trials of 0.5), 0.95 and 1.01, at
+// 149 to 180 0.76 (1024 channels in no order), 0.91 (4096 x 1150 trials of 0.1), 0.93 and 1.07. The
+// line keeps the direct-read form for most of these.
 constexpr double kShDirectClk = 140.0;
 // An FP32 plan of more than kShLdsTrials trials whose LDS form keeps its best tiling (14 wavefronts
 // of 4 trials: windows of up to 1024 words) takes that form where the shared-sum form's estimated
@@ -224,7 +227,9 @@ struct WsLayout {
 WsLayout workspace_layout(const dd_plan* p, int64_t n, bool linear = true);
 int64_t ring_table_bytes(const dd_plan* p);
 // Samples after a ring row's R that mirror its start, so no channel window the kernel
-// reads (at most launch.L + 3 samples from any start in [0, R)) wraps.
+// reads (at most launch.L + 3 samples from any start in [0, R), or the shared-sum form's
+// sh.mirror) wraps. A mirror longer than R is filled for R samples only: what lies past them no
+// stored output of a window looks at.
 inline int64_t ring_mirror(const dd_plan* p) {
   return std::max<int64_t>((int64_t)p->launch.L + 64, p->sh.on ? p->sh.mirror : 0);
 }

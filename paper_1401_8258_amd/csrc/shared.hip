@@ -29,7 +29,8 @@
 // What bounds it: instruction issue and LDS together. FP32, 1024 channels x 2048 trials, per 4
 // channels of 32 trials x 1008 samples: 1376 clocks of a CU, of which LDS is busy about 840
 // (16 bytes a lane read in 4.2 clocks, written in 13.9) and each SIMD issues vector
-// instructions for 935. HBM traffic is under a twentieth of the time. Measured and not kept:
+// instructions for 935. HBM carries 66 GB a launch (the input is 4.3 GB), 1.8 TB/s, a third of a
+// copy's rate. Measured and not kept:
 // - wavefronts that only form beside ones that only add (12 + 4): bound by the forming ones,
 //   101 ms against 59 at the time; all 16 doing both fills the waits of either part;
 // - 12 wavefronts of 3 trials with 168 registers: 44.5 ms against 37.3 with 16 of 2;
@@ -37,9 +38,9 @@
 //   grow by many samples a trial, which is what plan_shared weighs;
 // - asking for the records' cache lines ahead of their loads: no difference.
 // Times before (the LDS form for FP32 and FP16, the direct-read form for 8-bit) and now:
-//   1024 channels x 2048 trials, 408-428 MHz, FP32, 262144 samples   99.6 -> 37.3 ms
-//   the same band, 8-bit, 1024 channels x 2048 trials                22.6 -> 5.9 ms
-//   4096 channels x 750 trials of a low band, 8-bit                  22.0 -> 10.9 ms
+//   FP32, 408-428 MHz, 1024 channels x 1,048,576 samples x 2048 trials   97.2 -> 37.1 ms
+//   8-bit, the same band, 1024 x 262,144 x 2000                          22.6 -> 5.9 ms
+//   8-bit, 120-180 MHz, 4096 x 200,003 x 750                             22.0 -> 10.9 ms
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
